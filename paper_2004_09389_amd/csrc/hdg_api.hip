@@ -274,17 +274,12 @@ void op_sweep(hdg_ctx *c, int nb, int prec, const double *x, const double *z0, c
 // One P1 geometric-multigrid V-cycle on level l (input lev[l].b); returns the
 // buffer holding the result.  Damped-Jacobi pre-smoothing (first two sweeps
 // fused), residual, restriction, recursion, prolongation, post-smoothing.
-// Levels small enough for the tail kernel are handled by it in one launch,
-// dense coarsest solve included.  f32: the level vectors hold float values
+// The levels up to p1_dense.top are one dense product.  f32: the level vectors hold float values
 // (inside a V-cycle whose trace vectors are FP32, the P1 vectors are too).
 double *p1_vcycle(hdg_ctx *c, int l, int nb, hipStream_t s, bool f32) {
     hdg::P1LevelDev &L = c->lev[l];
-    if (l == c->tail_top && (int64_t)nb * L.n <= hdg::P1_TAIL_MAX) {   // one workgroup: few values only
-        hdg::launch_p1_tail(c->tail, nb, s, f32);
-        return L.x;
-    }
-    if (l == 0) {
-        hdg::launch_dense_mv(L.n, nb, c->coarse_inv, L.b, L.x, s, f32);
+    if (l == c->p1_dense.top) {
+        hdg::launch_dense(c->p1_dense.map, nb, L.b, L.x, s, f32);
         return L.x;
     }
     const double w = c->opt.p1_omega;
@@ -359,7 +354,7 @@ void restrict_p1(hdg_ctx *c, int nb, const double *res, double *rc, hipStream_t 
 double *rt_vcycle(hdg_ctx *c, int l, int nb, hipStream_t s, bool *pending) {
     hdg::Rt0LevelDev &L = c->rt[l];
     if (l == 0) {
-        hdg::launch_dense_mv(L.ne, nb, c->rt_coarse_inv, L.b, L.x, s);
+        hdg::launch_dense(c->rt_coarse, nb, L.b, L.x, s);
         *pending = false;
         return L.x;
     }
@@ -1150,7 +1145,9 @@ void setup_impl(const hdg_mesh *levels, int nlev, const int32_t *const *parents,
         HDG_REQUIRE(H[0].ne <= 8192, "coarsest RT0 level must have at most 8192 facets");
         std::vector<double> dense = hdg::rt0_dense(H[0]);
         if (!hdg::spd_inverse(dense, H[0].ne)) throw Error{HDG_EINVAL, "coarsest RT0 operator is singular"};
-        c->rt_coarse_inv = dev_upload(c, dense);
+        double *inv = dev_upload(c, dense);
+        c->rt_coarse = hdg::make_dense(c, H[0].ne, inv);
+        dev_release(c, inv, dense.size() * sizeof(double));
         c->rt.resize(nrt);
         int max_nv = 1;
         for (int l = 0; l < nrt; ++l) {
@@ -1220,25 +1217,10 @@ void setup_impl(const hdg_mesh *levels, int nlev, const int32_t *const *parents,
         if (opt.persistent && nv <= hdg::SMALL_P1_DENSE) p1B = hdg::p1_vcycle_matrix(ops, parents, opt.p1_nu, opt.p1_omega);
     }
 
-    // ---- tail of the P1 hierarchy (levels small enough for one workgroup)
-    // (one workgroup also reads the dense coarsest inverse: only for a small coarsest level)
-    c->tail_top = -1;
-    if (!c->lev.empty() && c->lev[0].n <= hdg::P1_TAIL_DENSE_MAX)   // (no P1 hierarchy with the LF flux)
-        for (int l = 0; l < (int)c->lev.size() && l < hdg::P1_TAIL_LEVELS; ++l)
-            if (c->lev[l].n <= opt.p1_tail_max) c->tail_top = l;
-            else break;
-    if (c->tail_top >= 0) {
-        hdg::P1Tail &T = c->tail;
-        T.top = c->tail_top;
-        T.nu = opt.p1_nu;
-        T.omega = opt.p1_omega;
-        T.Ainv = c->coarse_inv;
-        for (int l = 0; l <= c->tail_top; ++l) {
-            const hdg::P1LevelDev &L = c->lev[l];
-            T.lev[l] = hdg::P1Lev{L.n, L.w, L.col, L.val, L.diag, L.dinv, L.parents, L.crow, L.ccol, L.cw,
-                                  L.b, L.x, L.y};
-        }
-    }
+    // ---- the small P1 levels as one dense product (no P1 hierarchy with the LF flux)
+    if (!c->lev.empty())
+        c->p1_dense = hdg::collapse_p1(c, c->lev, c->coarse_inv, hdg::p1_collapse_max(c),
+                                       opt.p1_nu, opt.p1_omega);
 
     // ---- work vectors
     const size_t vl = (size_t)ne * m * mr;
@@ -1298,7 +1280,7 @@ void setup_impl(const hdg_mesh *levels, int nlev, const int32_t *const *parents,
     c->stage_rhat = dev_alloc<double>(c, vl);
 
     // ---- persistent single-launch solve: every trace and P1 vector of one solve in one workgroup's LDS
-    if (!lf && opt.persistent && (int)c->lev.size() <= hdg::P1_TAIL_LEVELS) {
+    if (!lf && opt.persistent && (int)c->lev.size() <= hdg::SMALL_LEVELS) {
         std::vector<hdg::P1Lev> lv;
         for (auto &L : c->lev) lv.push_back(hdg::P1Lev{L.n, L.w, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                                                         nullptr, nullptr, nullptr, nullptr, nullptr});
@@ -1362,6 +1344,10 @@ void setup_impl(const hdg_mesh *levels, int nlev, const int32_t *const *parents,
         }
     }
     HDG_HIP_CHECK(hipDeviceSynchronize());
+    if (!c->small_ok && c->coarse_inv) {   // the packed map replaces it
+        dev_release(c, c->coarse_inv, sizeof(double) * (size_t)c->lev[0].n * c->lev[0].n);
+        c->coarse_inv = nullptr;
+    }
     if (c->opt.smoother == HDG_SMOOTH_CHEBYSHEV) estimate_lambda_max(c);
 }
 
@@ -1464,7 +1450,89 @@ void hdg::build_p1_levels(hdg_ctx *c, const hdg_mesh *levels, const int32_t *con
     }
 }
 
+int hdg::p1_collapse_max(const hdg_ctx *c) {
+    const double m = c->m, stream = 8.0 * c->n_facet * m * (9.0 * m + 24.0 * c->opt.max_rhs);
+    const double fit = std::sqrt(std::max(0.0, 192.0 * 1048576.0 - stream) / 8.0);
+    return std::min(c->opt.p1_tail_max, std::clamp((int)fit, P1_COLLAPSE_MIN, P1_COLLAPSE_MAX));
+}
+
+constexpr int COLLAPSE_COLS = 64;   // unit vectors per pass of collapse_p1
+
+double *hdg::p1_cycle(std::vector<hdg::P1LevelDev> &lev, const hdg::P1Dense &dense, int l, int nb, int nu, double w,
+                      hipStream_t s) {
+    hdg::P1LevelDev &L = lev[l];
+    if (l == dense.top) {
+        hdg::launch_dense(dense.map, nb, L.b, L.x, s);
+        return L.x;
+    }
+    double *x = L.x, *y = L.y;
+    if (nu == 1) {
+        hdg::launch_p1_first(L.n, nb, L.dinv, w, L.b, x, s);
+    } else {
+        hdg::launch_p1_pre2(L.n, L.w, nb, L.col, L.val, L.diag, L.dinv, w, L.b, x, s);
+        for (int k = 2; k < nu; ++k) {
+            hdg::launch_p1_sweep(L.n, L.w, nb, L.col, L.val, L.diag, L.dinv, w, L.b, x, nullptr, nullptr, y, s);
+            std::swap(x, y);
+        }
+    }
+    hdg::launch_p1_resid(L.n, L.w, nb, L.col, L.val, L.diag, L.b, x, y, s);
+    hdg::P1LevelDev &C = lev[l - 1];
+    hdg::launch_p1_restrict(C.n, nb, L.crow, L.ccol, L.cw, y, C.b, s);
+    const double *xc = hdg::p1_cycle(lev, dense, l - 1, nb, nu, w, s);
+    for (int k = 0; k < nu; ++k) {
+        hdg::launch_p1_sweep(L.n, L.w, nb, L.col, L.val, L.diag, L.dinv, w, L.b, x, k == 0 ? xc : nullptr, L.parents,
+                             y, s);
+        std::swap(x, y);
+    }
+    return x;
+}
+
+hdg::DenseMap hdg::make_dense(hdg_ctx *c, int n, const double *src) {
+    hdg::DenseMap d;
+    const size_t nB = hdg::dense_doubles(n);
+    d.n = n;
+    d.B = dev_alloc<double>(c, nB);
+    HDG_HIP_CHECK(hipMemset(d.B, 0, nB * sizeof(double)));
+    if (src) hdg::launch_dense_cols(n, 0, n, src, d.B, nullptr);
+    check_launch();
+    HDG_HIP_CHECK(hipDeviceSynchronize());
+    return d;
+}
+
+hdg::P1Dense hdg::collapse_p1(hdg_ctx *c, const std::vector<hdg::P1LevelDev> &lev, const double *inv, int max_n, int nu,
+                              double w) {
+    hdg::P1Dense d;
+    d.map = hdg::make_dense(c, lev[0].n, inv);
+    int top = 0;
+    while (top + 1 < (int)lev.size() && lev[top + 1].n <= max_n) ++top;
+    if (top == 0) return d;
+    // the V-cycle applied to unit vectors, NCOL at a time, in work vectors of its own
+    constexpr int NCOL = COLLAPSE_COLS;
+    std::vector<hdg::P1LevelDev> t(lev.begin(), lev.begin() + top + 1);
+    for (auto &L : t) {
+        L.b = dev_alloc<double>(c, (size_t)3 * L.n * NCOL);
+        L.x = L.b + (size_t)L.n * NCOL;
+        L.y = L.x + (size_t)L.n * NCOL;
+    }
+    const int n = t[top].n;
+    hdg::P1Dense r;
+    r.top = top;
+    r.map = hdg::make_dense(c, n, nullptr);
+    for (int j = 0; j < n; j += NCOL) {
+        const int nc = std::min(NCOL, n - j);
+        hdg::launch_unit_cols(n, j, nc, t[top].b, nullptr);
+        const double *x = hdg::p1_cycle(t, d, top, nc, nu, w, nullptr);
+        hdg::launch_dense_cols(n, j, nc, x, r.map.B, nullptr);
+    }
+    check_launch();
+    HDG_HIP_CHECK(hipDeviceSynchronize());
+    for (auto &L : t) dev_release(c, L.b, sizeof(double) * 3 * (size_t)L.n * NCOL);
+    dev_release(c, d.map.B, sizeof(double) * hdg::dense_doubles(lev[0].n));
+    return r;
+}
+
 void *hdg::ctx_alloc(hdg_ctx *c, size_t bytes) { return dev_alloc<char>(c, bytes); }
+void hdg::ctx_release(hdg_ctx *c, void *p, size_t bytes) { dev_release(c, p, bytes); }
 int hdg::guarded(const std::function<void()> &fn) { return guard(fn); }
 void hdg::check_kernel_launch() { check_launch(); }
 void hdg::check_abi(int rc) {

@@ -395,35 +395,6 @@ void s_apply(const Dgs &g, const double *x, double *y) {
     lin(g, 0, 1, 1.0, t1, -1.0, t3, false, y);            // y_phi = A_pp x - A_pu D^-1 A_up x
 }
 
-double *p1_cycle(std::vector<P1LevelDev> &lev, const double *coarse_inv, int l, int nb, int nu, double w,
-                 hipStream_t s) {
-    P1LevelDev &L = lev[l];
-    if (l == 0) {
-        launch_dense_mv(L.n, nb, coarse_inv, L.b, L.x, s);
-        return L.x;
-    }
-    double *x = L.x, *y = L.y;
-    if (nu == 1) {
-        launch_p1_first(L.n, nb, L.dinv, w, L.b, x, s);
-    } else {
-        launch_p1_pre2(L.n, L.w, nb, L.col, L.val, L.diag, L.dinv, w, L.b, x, s);
-        for (int k = 2; k < nu; ++k) {
-            launch_p1_sweep(L.n, L.w, nb, L.col, L.val, L.diag, L.dinv, w, L.b, x, nullptr, nullptr, y, s);
-            std::swap(x, y);
-        }
-    }
-    launch_p1_resid(L.n, L.w, nb, L.col, L.val, L.diag, L.b, x, y, s);
-    P1LevelDev &C = lev[l - 1];
-    launch_p1_restrict(C.n, nb, L.crow, L.ccol, L.cw, y, C.b, s);
-    const double *xc = p1_cycle(lev, coarse_inv, l - 1, nb, nu, w, s);
-    for (int k = 0; k < nu; ++k) {
-        launch_p1_sweep(L.n, L.w, nb, L.col, L.val, L.diag, L.dinv, w, L.b, x, k == 0 ? xc : nullptr, L.parents, y,
-                        s);
-        std::swap(x, y);
-    }
-    return x;
-}
-
 // k Chebyshev steps for S x = b (phi fields; x updated in place), preconditioned by
 // the own-block inverses on [0.1, 1.1] lambda_max.  Uses tmp 3, 4, 5 (and 6, 7).
 void chebyshev(const Dgs &g, const double *b, double *x, int k, bool x_zero) {
@@ -473,7 +444,7 @@ void s_cycle(const Dgs &g, const double *b, double *x) {
         default: RESTRICT(3); break;
     }
     check_kernel_launch();
-    const double *xc = p1_cycle(c->dgs_lev, c->dgs_coarse_inv, L, g.nb, c->opt.p1_nu, c->opt.p1_omega, g.s);
+    const double *xc = p1_cycle(c->dgs_lev, c->dgs_dense, L, g.nb, c->opt.p1_nu, c->opt.p1_omega, g.s);
     switch (c->p) {
         case 1: PROLONG(1); break;
         case 2: PROLONG(2); break;
@@ -643,7 +614,10 @@ extern "C" int hdg_dgs_setup(hdg_ctx *c, const hdg_mesh *levels, int32_t n_level
             HDG_REQUIRE(parents && parents[l], "parents[l] must be given for every level above the coarsest");
             ops[l - 1] = hdg::galerkin_coarsen(ops[l], parents[l], levels[l - 1].n_vert);
         }
-        hdg::build_p1_levels(c, levels, parents, ops, c->dgs_lev, &c->dgs_coarse_inv);
+        double *inv = nullptr;
+        hdg::build_p1_levels(c, levels, parents, ops, c->dgs_lev, &inv);
+        c->dgs_dense = hdg::collapse_p1(c, c->dgs_lev, inv, hdg::p1_collapse_max(c), c->opt.p1_nu, c->opt.p1_omega);
+        hdg::ctx_release(c, inv, sizeof(double) * (size_t)c->dgs_lev[0].n * c->dgs_lev[0].n);
 
         // vertex <-> cell incidence
         std::vector<int32_t> cv(fine.cell_vert, fine.cell_vert + 3 * NK);

@@ -44,9 +44,20 @@ struct P1LevelDev {
     double *b = nullptr, *x = nullptr, *y = nullptr;  // [n][max_rhs] work vectors
 };
 
-constexpr int P1_TAIL_MAX = 4096;   // levels up to this many vertices run in the tail kernel
-constexpr int P1_TAIL_DENSE_MAX = 256;   // the tail also takes the dense coarsest product: only this small
-constexpr int P1_TAIL_LEVELS = 8;
+constexpr int P1_TAIL_MAX = 4096;       // upper bound of the option p1_tail_max
+// The P1 levels of at most p1_collapse_max vertices, taken together, are one dense product
+// (k_dense) instead of 4-6 launches of 4-5 us for each of them.  The product reads 8 n^2 bytes,
+// so the line lies where that takes about as long as the launches it replaces, and that
+// depends on where the matrix is found.  In the Infinity Cache: V-cycle of the level-5 sphere
+// (p = 1, FP64, 1 / 6 / 16 right-hand sides) with its 2562-vertex level collapsed
+// 48 / 62 / 76 us, its 642-vertex level 49 / 69 / 85 us, none 59 / 87 / 102 us; 56x56 torus
+// (p = 2, 1 / 4) with its 3136-vertex level 38.8 / 65 us, its 784-vertex level 37.0 / 61 us.
+// In HBM (level-6 sphere, p = 2, 16 right-hand sides, whose vectors fill that cache): a
+// solve with 2562 vertices collapsed 3868 us, 642 vertices 3763 us.  Hence what the operator
+// rows and about 24 vectors leave free of 192 MiB, between 1100 (10 MB) and 2600 vertices.
+constexpr int P1_COLLAPSE_MIN = 1100, P1_COLLAPSE_MAX = 2600;
+int p1_collapse_max(const hdg_ctx *c);
+constexpr int SMALL_LEVELS = 8;         // P1 levels of the single-launch solve
 
 struct P1Lev {
     int n, w;
@@ -58,11 +69,16 @@ struct P1Lev {
     double *b, *x, *y;
 };
 
-struct P1Tail {
-    int top, nu;
-    double omega;
-    const double *Ainv;                      // dense inverse of level 0
-    P1Lev lev[P1_TAIL_LEVELS];
+// A dense map x = B b (launch_dense), B padded with zeros to dense_doubles(n) entries
+struct DenseMap {
+    int n = 0;
+    double *B = nullptr;
+};
+// The P1 V-cycle from level `top` down as one dense map (top = 0: the inverse of
+// the coarsest operator).
+struct P1Dense {
+    DenseMap map;
+    int top = 0;
 };
 
 // RT0 level on the device (Lax-Friedrichs coarse space), arrays as in Rt0Host
@@ -89,8 +105,17 @@ void check_abi(int rc);
 // upload P1 operators (coarse to fine) with transfers and the coarsest dense inverse (hdg_api.hip)
 void build_p1_levels(hdg_ctx *c, const hdg_mesh *levels, const int32_t *const *parents,
                      const std::vector<P1Host> &ops, std::vector<P1LevelDev> &lev, double **coarse_inv);
+// one V-cycle on level l (input lev[l].b, FP64); returns the buffer holding the result
+double *p1_cycle(std::vector<P1LevelDev> &lev, const P1Dense &dense, int l, int nb, int nu, double w, hipStream_t s);
+// The largest level of at most max_n vertices as a dense map: the V-cycle with nu sweeps of
+// damping w applied to unit vectors.  inv: the coarsest inverse, row-major (device); synchronous.
+P1Dense collapse_p1(hdg_ctx *c, const std::vector<P1LevelDev> &lev, const double *inv, int max_n, int nu, double w);
+// an n x n dense map of the context from a row-major device matrix (src null: zeros); synchronous
+DenseMap make_dense(hdg_ctx *c, int n, const double *src);
 // device allocation owned by the context (freed by hdg_destroy)
 void *ctx_alloc(hdg_ctx *c, size_t bytes);
+// free one device allocation of the context
+void ctx_release(hdg_ctx *c, void *p, size_t bytes);
 // each side's share of the DG trace of the cell field q at its facet nodes (hdg_imex.hip):
 // half [n_facet][2][facet_dofs][nrhs]; phi = hscale * field 0
 void launch_dg_half(const hdg_ctx *c, int nb, double hscale, const double *q, double *half, hipStream_t s);
@@ -131,7 +156,7 @@ struct hdg_ctx {
     double *dgs_Dinv = nullptr;     // [n_cell][2n]      1 / diag(A_uu)
     double dgs_lmax = 0.0;          // eigenvalue estimate of S_own^-1 S
     std::vector<hdg::P1LevelDev> dgs_lev;   // Galerkin P1 hierarchy of S (level 0 coarsest)
-    double *dgs_coarse_inv = nullptr;
+    hdg::P1Dense dgs_dense;                 // its small levels as one dense product
     int32_t *dgs_cvert = nullptr;   // [n_cell][3] vertex ids
     int32_t *dgs_vrow = nullptr, *dgs_vcol = nullptr;  // vertex -> 3 * cell + corner CSR
     double *dgs_half = nullptr, *dgs_lam = nullptr;    // trace shares and trace of the apply
@@ -156,14 +181,13 @@ struct hdg_ctx {
 
     // P1 hierarchy, level 0 coarsest
     std::vector<hdg::P1LevelDev> lev;
-    double *coarse_inv = nullptr;   // dense inverse of the coarsest level
-    int tail_top = -1;              // levels 0..tail_top run in the single-workgroup tail kernel
-    hdg::P1Tail tail{};
+    double *coarse_inv = nullptr;   // inverse of the coarsest level, row-major (single-launch contexts only)
+    hdg::P1Dense p1_dense;          // levels 0..p1_dense.top as one dense product
 
     // Lax-Friedrichs coarse space: RT0 levels (level 0 coarsest), dense inverse of level 0,
     // prolongation weights onto the trace [5][m][n_facet] and the CSR of its transpose
     std::vector<hdg::Rt0LevelDev> rt;
-    double *rt_coarse_inv = nullptr;
+    hdg::DenseMap rt_coarse;                    // inverse of the coarsest level
     double *rt_corr = nullptr;                  // vertex-patch corrections [n_vert][RT_PV][max_rhs]
     double *lf_pw = nullptr;
     int32_t *lf_rrow = nullptr, *lf_rcol = nullptr;

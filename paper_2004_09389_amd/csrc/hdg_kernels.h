@@ -191,8 +191,12 @@ void launch_p1_restrict(int nc, int nb, const int *crow, const int *ccol, const 
 void launch_p1_resid_restrict(int n, int W, const int *col, const double *val, const double *diag, const double *b,
                               const double *x, int nc, const int *crow, const int *ccol, const double *cw, double *bc,
                               hipStream_t s, bool f32 = false);
-void launch_dense_mv(int n, int nb, const double *Ainv, const double *b, double *x, hipStream_t s, bool f32 = false);
-void launch_p1_tail(const P1Tail &T, int nb, hipStream_t s, bool f32 = false);
+// x = B b for a dense map; nb <= 64
+void launch_dense(const DenseMap &D, int nb, const double *b, double *x, hipStream_t s, bool f32 = false);
+int dense_ld(int n);                            // row stride of B
+size_t dense_doubles(int n);                    // entries of B, padding included
+void launch_dense_cols(int n, int col0, int ncol, const double *src, double *B, hipStream_t s);
+void launch_unit_cols(int n, int col0, int ncol, double *b, hipStream_t s);
 
 // cells: cells per block of the batched (nb >= 2) cell kernels; 0 = the most
 // that fit (256 threads, 64 KiB of staged rows), larger requests are clamped
@@ -292,7 +296,7 @@ struct SmallArgs {
     double omega, p1_omega, rtol;
     const double *S, *T, *Dw;           // FP64 facet rows (16-byte groups)
     const int *nbr, *fvert, *vf_row, *vf_col;
-    P1Lev lev[P1_TAIL_LEVELS];          // P1 levels, 0 coarsest (work vectors unused: LDS)
+    P1Lev lev[SMALL_LEVELS];          // P1 levels, 0 coarsest (work vectors unused: LDS)
     const double *Ainv;                 // dense inverse of level 0
     const double *p1B;                  // the whole P1 V-cycle as a matrix, transposed [j][i] (finest level), or null
     // Steps 1 and 3 inside the launch (stage solve)

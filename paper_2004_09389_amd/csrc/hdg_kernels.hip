@@ -659,9 +659,8 @@ __global__ void k_restrict_trace(int nv, int nb, const int *__restrict__ vf_row,
 // Coarse problem S_c q = r_c of the upwind case, solved by one geometric
 // multigrid V-cycle: damped Jacobi smoothing, linear-interpolation transfer
 // from the nested hierarchy's parent map, dense inverse on the coarsest
-// level.  Large levels run as one kernel per step; all levels with at most
-// P1_TAIL_MAX vertices (and the dense solve) run inside one single-workgroup
-// kernel, because at that size a launch costs more than the work.
+// level.  Large levels run as one kernel per step; the small levels together
+// are one dense product (k_dense).
 // The per-level kernels hand each XCD one contiguous range of vertices, so the
 // neighbour rows that nearby vertices share are fetched into one L2.
 
@@ -803,126 +802,6 @@ __global__ void k_p1_restrict(int nc, int nb, const int *__restrict__ crow, cons
     const int k0 = crow[c];
     bc[t] = (VT)acc_row<8>(0.0, crow[c + 1] - k0,
                            [&](int k) { return cw[k0 + k] * (double)r[(size_t)ccol[k0 + k] * nb + rr]; });
-}
-
-// x = Ainv b on the coarsest level when it is too large for the tail kernel:
-// one wavefront per (row, RHS), lanes stride over the row, shuffle reduction.
-// x = Ainv b on the coarsest level: one wavefront per (row, chunk of up to CH
-// right-hand sides), lanes striding the row; each matrix row is read once per
-// chunk and a lane reads the chunk's values of b[j] contiguously.
-template <int CH, typename VT>
-__global__ void k_dense_mv(int n, int nb, const double *__restrict__ Ainv, const VT *__restrict__ b,
-                           VT *__restrict__ x) {
-    const int nch = (nb + CH - 1) / CH;
-    const int w = (blockIdx.x * blockDim.x + threadIdx.x) / 64;
-    const int lane = threadIdx.x & 63;
-    if (w >= n * nch) return;
-    const int i = w / nch, r0 = (w - i * nch) * CH;
-    const int cnt = min(CH, nb - r0);
-    double s[CH];
-#pragma unroll
-    for (int q = 0; q < CH; ++q) s[q] = 0.0;
-    for (int j = lane; j < n; j += 64) {
-        const double a = Ainv[(size_t)i * n + j];
-        const VT *bj = b + (size_t)j * nb + r0;
-#pragma unroll
-        for (int q = 0; q < CH; ++q)
-            if (q < cnt) s[q] += a * (double)bj[q];
-    }
-#pragma unroll
-    for (int q = 0; q < CH; ++q)
-        for (int off = 32; off > 0; off >>= 1) s[q] += __shfl_xor(s[q], off, 64);
-    if (lane == 0)
-#pragma unroll
-        for (int q = 0; q < CH; ++q)
-            if (q < cnt) x[(size_t)i * nb + r0 + q] = (VT)s[q];
-}
-
-// All levels 0..top of the hierarchy in one workgroup: the complete V-cycle
-// below and including level `top`, input lev[top].b, result in lev[top].x.
-template <typename VT>
-__global__ __launch_bounds__(1024) void k_p1_tail(const P1Tail Targ, int nb) {
-    __shared__ VT *xs[P1_TAIL_LEVELS];
-    __shared__ P1Tail T;   // level descriptors staged in LDS (runtime-indexed below)
-    const int tid = threadIdx.x, nth = blockDim.x;
-    if (tid == 0) T = Targ;
-    __syncthreads();
-    const double w = T.omega;
-    for (int l = T.top; l >= 1; --l) {
-        const P1Lev &L = T.lev[l];
-        const int N = L.n * nb;
-        const VT *b = reinterpret_cast<const VT *>(L.b);
-        VT *x = reinterpret_cast<VT *>(L.x), *y = reinterpret_cast<VT *>(L.y);
-        for (int t = tid; t < N; t += nth) x[t] = (VT)(w * L.dinv[t / nb] * (double)b[t]);
-        __syncthreads();
-        for (int k = 1; k < T.nu; ++k) {
-            for (int t = tid; t < N; t += nth) {
-                const int v = t / nb, r = t - v * nb;
-                y[t] = (VT)((double)x[t] + w * L.dinv[v] * ((double)b[t] - p1_ax<0>(v, L.n, L.w, nb, r, L.col, L.val, L.diag, x)));
-            }
-            __syncthreads();
-            VT *tmp = x; x = y; y = tmp;
-        }
-        for (int t = tid; t < N; t += nth) {
-            const int v = t / nb, r = t - v * nb;
-            y[t] = (VT)((double)b[t] - p1_ax<0>(v, L.n, L.w, nb, r, L.col, L.val, L.diag, x));
-        }
-        __syncthreads();
-        const P1Lev &C = T.lev[l - 1];
-        for (int t = tid; t < C.n * nb; t += nth) {
-            const int c = t / nb, rr = t - c * nb;
-            double acc = 0.0;
-            for (int k = L.crow[c]; k < L.crow[c + 1]; ++k) acc += L.cw[k] * (double)y[(size_t)L.ccol[k] * nb + rr];
-            reinterpret_cast<VT *>(C.b)[t] = (VT)acc;
-        }
-        if (tid == 0) xs[l] = x;
-        __syncthreads();
-    }
-    {
-        const P1Lev &L0 = T.lev[0];
-        const int n0 = L0.n;
-        for (int t = tid; t < n0 * nb; t += nth) {
-            const int i = t / nb, r = t - i * nb;
-            double s = 0.0;
-            for (int j = 0; j < n0; ++j) s += T.Ainv[(size_t)i * n0 + j] * (double)reinterpret_cast<const VT *>(L0.b)[(size_t)j * nb + r];
-            reinterpret_cast<VT *>(L0.x)[t] = (VT)s;
-        }
-        if (tid == 0) xs[0] = reinterpret_cast<VT *>(L0.x);
-        __syncthreads();
-    }
-    for (int l = 1; l <= T.top; ++l) {
-        const P1Lev &L = T.lev[l];
-        const int N = L.n * nb;
-        const VT *b = reinterpret_cast<const VT *>(L.b);
-        VT *x = xs[l];
-        VT *y = (x == reinterpret_cast<VT *>(L.x)) ? reinterpret_cast<VT *>(L.y) : reinterpret_cast<VT *>(L.x);
-        const VT *xc = xs[l - 1];
-        for (int k = 0; k < T.nu; ++k) {
-            for (int t = tid; t < N; t += nth) {
-                const int v = t / nb, r = t - v * nb;
-                auto xin = [&](int u) -> double {
-                    double s = (double)x[(size_t)u * nb + r];
-                    if (k == 0)
-                        s += 0.5 * ((double)xc[(size_t)L.parents[2 * u] * nb + r] +
-                                    (double)xc[(size_t)L.parents[2 * u + 1] * nb + r]);
-                    return s;
-                };
-                double ax = 0.0;
-                for (int k = 0; k < L.w; ++k) ax += L.val[(size_t)k * L.n + v] * xin(L.col[(size_t)k * L.n + v]);
-                const double xv = xin(v);
-                ax += L.diag[v] * xv;
-                y[t] = (VT)(xv + w * L.dinv[v] * ((double)b[t] - ax));
-            }
-            __syncthreads();
-            VT *tmp = x; x = y; y = tmp;
-        }
-        if (tid == 0) xs[l] = x;
-        __syncthreads();
-    }
-    const P1Lev &Lt = T.lev[T.top];
-    if (T.top > 0 && xs[T.top] != reinterpret_cast<VT *>(Lt.x)) {
-        for (int t = tid; t < Lt.n * nb; t += nth) reinterpret_cast<VT *>(Lt.x)[t] = xs[T.top][t];
-    }
 }
 
 // ------------------------------------------------------------------ condensation / recovery (per solve)
@@ -1791,47 +1670,153 @@ __global__ void k_p1_restrict4(int nc, int nb, const int *__restrict__ crow, con
     p1_st4(bc + (size_t)c * nb + r0, s);
 }
 
-// x = Ainv b on the coarsest level, one 256-thread block per row i.  A thread
-// takes G consecutive right-hand sides (G = 4 when nb = 4 NQ with NQ a power of
-// two, G = 1 when nb = 1) and one of the block's 256 / NQ phases j = phase +
-// k (256 / NQ), four columns' loads in flight at a time.  The partial sums are
-// combined by a butterfly within each wavefront and then over the four
-// wavefronts in order: a fixed summation order for a given nb.
-template <int G, typename VT>
-__global__ __launch_bounds__(256) void k_dense_row(int n, int nb, const double *__restrict__ Ainv,
+// ---------------------------------------------------------------- dense level products
+//
+// x = B b with B the dense map of a coarse level: the inverse of the coarsest
+// operator, or a whole V-cycle below a level collapsed into one matrix.  B
+// (8 n^2 bytes, row-major, rows padded to dense_ld(n) entries with zeros, the
+// row count to a multiple of 16) is read once per call and is the cost.
+//
+// One right-hand side: one block per row, 16-byte loads, a butterfly in each
+// wavefront, then the four wavefronts in order (1024 rows 4.1 us, 2562 rows 11.4 us
+// = 4.6 TB/s).
+//
+// More: a block takes 4 R rows, its 8 wavefronts the chunks of 32 columns in turn.
+// Lane (i, k) = (lane % 4, lane / 4) loads B[row i][2 k], B[row i][2 k + 1] of the
+// chunk (16 bytes; 256 contiguous bytes of each row per wavefront) and the four
+// right-hand sides 4 i .. 4 i + 3 of those two entries of b (T such groups of 16).
+// v_mfma_f64_4x4x4_4b multiplies four 4 x 4 x 4 blocks: here four slices of the same
+// rows' columns, so its 16 column indices are simply the lanes' k (the order of the
+// columns in a sum is free, and A and B use the same one) and the four results are
+// added by two shuffles.  The wavefronts' sums are added through LDS in order:
+// repeated products are bitwise equal.  1024 rows: 4.0 us at 16 right-hand sides, 4.9 us at
+// 6; 2562 rows, where the 52 MB of B bound it: 16.0, 17.8 and (32) 22.7 us; the
+// 784-vertex level of the 56x56 torus and those below it 5.2 us, 74 us in one workgroup.
+// Small row tiles because the matrix cores of a CU are the limit up to about 1100 rows
+// (642 rows, 16 right-hand sides: 4.6 us, with 16 x 16 tiles on 41 CUs 6.2 us).  Splitting the
+// columns over several blocks instead, the last of which adds the partial tiles, was
+// 5 times slower: the device-scope fence before the arrival counter writes back
+// each XCD's L2.
+template <typename VT>
+__global__ __launch_bounds__(256) void k_dense_row(int n, int ld, const double *__restrict__ B,
                                                    const VT *__restrict__ b, VT *__restrict__ x) {
-    __shared__ double part[4][64];
-    const int i = blockIdx.x, tid = threadIdx.x;
-    const int NQ = nb / G, JP = 256 / NQ;
-    const int rq = tid & (NQ - 1), jp = tid / NQ, r0 = rq * G;
-    const double *Ai = Ainv + (size_t)i * n;
-    double s[G];
+    constexpr int U = 4;
+    __shared__ double part[4];
+    const int tid = threadIdx.x;
+    const double *Bi = B + (size_t)blockIdx.x * ld;
+    double s = 0.0;
+    for (int j0 = 2 * tid; j0 < ld; j0 += U * 512) {
+        dbl2_t a[U];
+        double b0[U], b1[U];
 #pragma unroll
-    for (int g = 0; g < G; ++g) s[g] = 0.0;
-    for (int j0 = jp; j0 < n; j0 += 4 * JP) {
-        double a[4], bv[4][G];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int j = min(j0 + u * JP, n - 1);
-            a[u] = Ai[j];
-            if constexpr (G == 4) load_rb<4>(b + (size_t)j * nb + r0, bv[u]);
-            else bv[u][0] = (double)b[j];
+        for (int u = 0; u < U; ++u) {
+            const int j = j0 + u * 512;
+            a[u] = j < ld ? *reinterpret_cast<const dbl2_t *>(Bi + j) : dbl2_t{0.0, 0.0};
+            b0[u] = (double)b[min(j, n - 1)];   // columns past n meet zeros of B
+            b1[u] = (double)b[min(j + 1, n - 1)];
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (j0 + u * JP < n)
-#pragma unroll
-                for (int g = 0; g < G; ++g) s[g] += a[u] * bv[u][g];
+        for (int u = 0; u < U; ++u) {
+            s += a[u].x * b0[u];
+            s += a[u].y * b1[u];
+        }
     }
-    for (int off = NQ; off < 64; off <<= 1)
-#pragma unroll
-        for (int g = 0; g < G; ++g) s[g] += __shfl_xor(s[g], off, 64);
-    const int wv = tid >> 6, lane = tid & 63;
-    if (lane < NQ)
-#pragma unroll
-        for (int g = 0; g < G; ++g) part[wv][lane * G + g] = s[g];
+    for (int off = 1; off < 64; off <<= 1) s += __shfl_xor(s, off, 64);
+    if ((tid & 63) == 0) part[tid >> 6] = s;
     __syncthreads();
-    if (tid < nb) x[(size_t)i * nb + tid] = (VT)(((part[0][tid] + part[1][tid]) + part[2][tid]) + part[3][tid]);
+    if (tid == 0) x[blockIdx.x] = (VT)(((part[0] + part[1]) + part[2]) + part[3]);
+}
+
+constexpr int DENSE_WAVES = 8;
+
+template <int R, int T, typename VT>
+__global__ __launch_bounds__(64 * DENSE_WAVES) void k_dense(int n, int ld, int nb, const double *__restrict__ B,
+                                                            const VT *__restrict__ b, VT *__restrict__ x) {
+    constexpr int W = DENSE_WAVES, U = T == 1 ? 2 : 1;
+    __shared__ double part[W][R * T * 64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, i = lane & 3, kl = lane >> 2;
+    const int row0 = blockIdx.x * 4 * R, nch = (ld + 31) / 32;
+    const bool quad = nb % 4 == 0;   // aligned groups of four right-hand sides
+    double acc[R][T][4];
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[q][t][c] = 0.0;
+    for (int c0 = wv * U; c0 < nch; c0 += W * U) {
+        dbl2_t a[U][R];
+        VT bv[U][2][T][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k0 = 32 * (c0 + u) + 2 * kl;   // even; rows are padded to ld with zeros
+#pragma unroll
+            for (int q = 0; q < R; ++q)
+                a[u][q] = k0 < ld ? *reinterpret_cast<const dbl2_t *>(B + (size_t)(row0 + 4 * q + i) * ld + k0)
+                                  : dbl2_t{0.0, 0.0};
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const VT *bk = b + (size_t)min(k0 + h, n - 1) * nb;   // columns past n meet zeros of B
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    const int r = 16 * t + 4 * i;
+                    if (quad && r < nb) {
+                        load_raw<4>(bk + r, bv[u][h][t]);
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) bv[u][h][t][c] = r + c < nb ? bk[r + c] : VT(0);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int q = 0; q < R; ++q) {
+                        double v = acc[q][t][c];
+                        v = __builtin_amdgcn_mfma_f64_4x4x4f64(a[u][q].x, (double)bv[u][0][t][c], v, 0, 0, 0);
+                        acc[q][t][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[u][q].y, (double)bv[u][1][t][c], v, 0, 0, 0);
+                    }
+    }
+    // lane 16 i + 4 block + j holds (row i, right-hand side 4 j + c) of its block
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                double v = acc[q][t][c];
+                v += __shfl_xor(v, 4, 64);
+                v += __shfl_xor(v, 8, 64);
+                if ((lane & 12) == 0) part[wv][((4 * q + (lane >> 4)) * T + t) * 16 + 4 * i + c] = v;
+            }
+    __syncthreads();
+    for (int o = tid; o < R * T * 64; o += 64 * W) {
+        const int r = o % (16 * T), row = row0 + o / (16 * T);
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) s += part[w][o];
+        if (row < n && r < nb) x[(size_t)row * nb + r] = (VT)s;
+    }
+}
+
+// columns col0 .. col0 + ncol - 1 of a dense map (src [n][ncol]) into B
+__global__ void k_dense_cols(int n, int ld, int col0, int ncol, const double *__restrict__ src,
+                             double *__restrict__ B) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= (int64_t)n * ncol) return;
+    B[(size_t)(t / ncol) * ld + col0 + t % ncol] = src[t];
+}
+
+// b[v][q] = 1 where v = col0 + q, else 0 (ncol unit vectors)
+__global__ void k_unit_cols(int n, int col0, int ncol, double *__restrict__ b) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= (int64_t)n * ncol) return;
+    b[t] = t / ncol == col0 + t % ncol ? 1.0 : 0.0;
 }
 
 // y = S x or y = b - S x
@@ -2305,20 +2290,25 @@ void launch_p1_resid_restrict(int n, int W, const int *col, const double *val, c
 #undef RR
 }
 #undef P1_GRID
-// the row-block product for nb = 1 and nb = 4 NQ (NQ = 1, 2, 4, 8, 16), else a
-// wavefront per (row, chunk of 8 right-hand sides)
-void launch_dense_mv(int n, int nb, const double *Ainv, const double *b, double *x, hipStream_t s, bool f32) {
-    const int nq = nb / 4;
-    const bool g4 = nb % 4 == 0 && nq <= 16 && (nq & (nq - 1)) == 0;
-    P1_TYPED(if (nb == 1) hipLaunchKernelGGL((k_dense_row<1, VT>), dim3(n), dim3(256), 0, s, n, nb, Ainv, pv<VT>(b),
-                                              pv<VT>(x));
-             else if (g4) hipLaunchKernelGGL((k_dense_row<4, VT>), dim3(n), dim3(256), 0, s, n, nb, Ainv, pv<VT>(b),
-                                             pv<VT>(x));
-             else hipLaunchKernelGGL((k_dense_mv<8, VT>), GRID((int64_t)n * ((nb + 7) / 8) * 64, 256), 0, s, n, nb,
-                                     Ainv, pv<VT>(b), pv<VT>(x)))
+int dense_ld(int n) { return (n + 1) / 2 * 2; }
+size_t dense_doubles(int n) { return (size_t)((n + 15) / 16 * 16) * dense_ld(n); }
+void launch_dense(const DenseMap &D, int nb, const double *b, double *x, hipStream_t s, bool f32) {
+    const int n = D.n, ld = dense_ld(n);
+    // sixteen rows per block above 1100 rows, where B bounds the product and every block re-reads
+    // b (2562 rows, 6 / 32 right-hand sides: 17.8 / 22.7 us, four rows 22 / 26 us); four below,
+    // where more would leave CUs idle (1024 rows, 16: four 4.0 us, eight 5.3 us)
+#define DN(R, T) hipLaunchKernelGGL((k_dense<R, T, VT>), dim3((n + 4 * R - 1) / (4 * R)), dim3(64 * DENSE_WAVES), 0, s, n, \
+                                    ld, nb, D.B, pv<VT>(b), pv<VT>(x))
+    P1_TYPED(if (nb == 1) hipLaunchKernelGGL(k_dense_row<VT>, dim3(n), dim3(256), 0, s, n, ld, D.B, pv<VT>(b), pv<VT>(x));
+             else if (n <= 1100) { if (nb <= 16) DN(1, 1); else if (nb <= 32) DN(1, 2); else DN(1, 4); }
+             else if (nb <= 16) DN(4, 1); else if (nb <= 32) DN(4, 2); else DN(4, 4))
+#undef DN
 }
-void launch_p1_tail(const P1Tail &T, int nb, hipStream_t s, bool f32) {
-    P1_TYPED(hipLaunchKernelGGL(k_p1_tail<VT>, dim3(1), dim3(1024), 0, s, T, nb))
+void launch_dense_cols(int n, int col0, int ncol, const double *src, double *B, hipStream_t s) {
+    hipLaunchKernelGGL(k_dense_cols, GRID((int64_t)n * ncol, 256), 0, s, n, dense_ld(n), col0, ncol, src, B);
+}
+void launch_unit_cols(int n, int col0, int ncol, double *b, hipStream_t s) {
+    hipLaunchKernelGGL(k_unit_cols, GRID((int64_t)n * ncol, 256), 0, s, n, col0, ncol, b);
 }
 #undef P1_TYPED
 

@@ -102,7 +102,7 @@ __device__ __forceinline__ double oprd(const double *p) {
 struct Ops {
     const double *S, *T, *Dw, *Ainv, *B;
     const int *nbr, *fvert, *vf_row, *vf_col;
-    P1Lev lev[P1_TAIL_LEVELS];
+    P1Lev lev[SMALL_LEVELS];
 };
 
 // y = S x  (b == nullptr) or y = b - S x over this thread's facets; x in LDS
@@ -440,7 +440,7 @@ __device__ __forceinline__ double s_p1_ax(const P1Lev &L, int v, const lds_dbl *
 // runtime-indexed).  Which of x, y holds a level's iterate follows from the
 // sweep count alone, so no pointer has to be published between the phases.
 struct P1Vecs {
-    lds_dbl *b[P1_TAIL_LEVELS], *x[P1_TAIL_LEVELS], *y[P1_TAIL_LEVELS];
+    lds_dbl *b[SMALL_LEVELS], *x[SMALL_LEVELS], *y[SMALL_LEVELS];
 };
 
 // One P1 multigrid V-cycle from the finest level's right-hand side; returns the
