@@ -271,6 +271,26 @@ void op_sweep(hdg_ctx *c, int nb, int prec, const double *x, const double *z0, c
     check_launch();
 }
 
+// ------------------------------------------------------------------ cell passes
+
+// Step 1: rhat = sum_K R_K^T C_K A_K^-1 (r, v)_K, the cells' shares staged in loc
+void condense(hdg_ctx *c, int nb, const double *r_cell, double *loc, double *rhat, hipStream_t s, int cells) {
+    if (c->flux == HDG_FLUX_LF || c->cf.zt)
+        hdg::launch_condense_cell(c->p, c->nu, c->n_cell, nb, c->Zr, r_cell, loc, s, cells);
+    else
+        hdg::launch_cell_pass(c->p, false, c->n_cell, nb, c->cf, c->cell_facet, c->cell_rev, r_cell, nullptr, loc, s);
+    hdg::launch_condense_gather(c->p, c->nu, c->n_cell, c->n_facet, nb, loc, c->d_fcell, c->d_floc, rhat, s);
+}
+
+// Step 3: q = A^-1 ((r, v)_K - B lam)
+void recover(hdg_ctx *c, int nb, const double *r_cell, const double *lam, double *q_cell, hipStream_t s, int cells) {
+    if (c->flux == HDG_FLUX_LF)
+        hdg::launch_recover(c->p, c->nu, c->n_cell, nb, c->Ar, c->Wr, c->cell_facet, c->cell_rev, r_cell, lam, q_cell, s,
+                            cells);
+    else
+        hdg::launch_cell_pass(c->p, true, c->n_cell, nb, c->cf, c->cell_facet, c->cell_rev, r_cell, lam, q_cell, s);
+}
+
 // One P1 geometric-multigrid V-cycle on level l (input lev[l].b); returns the
 // buffer holding the result.  Damped-Jacobi pre-smoothing (first two sweeps
 // fused), residual, restriction, recursion, prolongation, post-smoothing.
@@ -1066,12 +1086,37 @@ void setup_impl(const hdg_mesh *levels, int nlev, const int32_t *const *parents,
     int *d_err = dev_alloc<int>(c, 1);
     HDG_HIP_CHECK(hipMemset(d_err, 0, sizeof(int)));
     double *Sloc = dev_alloc<double>(c, (size_t)c->nt * c->nt * nk);
-    c->Zr = dev_alloc<double>(c, (size_t)c->nt * hdg::cell_zw(c->p) * nk);
-    c->Ar = dev_alloc<double>(c, (size_t)c->nc * c->nc * nk);
-    c->Wr = dev_alloc<double>(c, (size_t)c->nc * c->nt * nk);
+    // the dense maps: Lax-Friedrichs, contexts whose trace vectors could fit the single-launch solve's LDS,
+    // and (the condensation's alone) f varying inside the cells
+    const bool vf = fine.geom == HDG_SPHERE && prm->omega != 0.0;
+    const bool dense = lf || (opt.persistent && (size_t)12 * ne * c->m * sizeof(double) <= 160 * 1024);
+    if (dense || vf) c->Zr = dev_alloc<double>(c, (size_t)c->nt * hdg::cell_zw(c->p) * nk);
+    if (dense) {
+        c->Ar = dev_alloc<double>(c, (size_t)c->nc * c->nc * nk);
+        c->Wr = dev_alloc<double>(c, (size_t)c->nc * c->nt * nk);
+    }
+    double *d_fs = nullptr, *d_geo = nullptr;
+    if (!lf) {
+        d_fs = dev_alloc<double>(c, (size_t)(vf ? c->n * hdg::wide_padded(c->nc, 2) : hdg::wide_padded(c->n * c->n, 2)) * nk);
+        d_geo = dev_alloc<double>(c, (size_t)hdg::CELL_GEO * nk);
+        c->cf.fs = d_fs;
+        c->cf.geo = d_geo;
+        c->cf.tab = dev_upload(c, hdg::cell_tables(R));
+        c->cf.hs = c->hscale;
+        c->qx = d_ref + R.M.size() + R.G.size() + R.E.size() + R.T.size() + R.F.size();
+        if (vf) {
+            double *zt = dev_alloc<double>(c, (size_t)2 * c->n * c->n * nk);
+            hdg::launch_cell_rot(c->p, nk, d_corners, d_ref, c->qx, c->cf.tab, c->dt, prm->f0, prm->omega, zt, s);
+            c->cf.zt = zt;
+        } else {
+            const double a = c->dt * prm->f0;   // 1 / (1 + i a)
+            c->cf.za = 1.0 / (1.0 + a * a);
+            c->cf.zb = -a / (1.0 + a * a);
+        }
+    }
     hdg::CellParams cp{c->kappa, c->tau, c->dt, prm->f0, prm->omega, c->hscale, fine.geom};
-    hdg::launch_cell_condense(c->p, c->nu, nk, d_corners, d_ref, cp, Sloc, c->Zr, c->Ar, c->Wr, d_err, s, nullptr,
-                              nullptr);
+    hdg::launch_cell_condense(c->p, c->nu, nk, d_corners, d_ref, cp, Sloc, c->Zr, c->Ar, c->Wr, d_fs, vf, d_geo,
+                              d_err, s);
     check_launch();
     HDG_HIP_CHECK(hipDeviceSynchronize());
     int herr = 0;
@@ -1632,8 +1677,7 @@ extern "C" int hdg_condense(hdg_ctx *c, int32_t nb, const double *r_cell, double
         hipStream_t s = as_stream(stream);
         Timed t(c, HDG_KERNEL_CONDENSE, HDG_FP64, s, nb);
         for (int rep = 0; rep < t.repeats(); ++rep)
-            hdg::launch_condense(c->p, c->nu, c->n_cell, c->n_facet, nb, c->Zr, r_cell, c->loc, c->d_fcell, c->d_floc, rhat,
-                                 s, c->cell_cells);
+            condense(c, nb, r_cell, c->loc, rhat, s, c->cell_cells);
         check_launch();
     });
 }
@@ -1649,8 +1693,7 @@ extern "C" int hdg_condense_noalloc(hdg_ctx *c, int32_t nb, const double *r_cell
                                         " doubles of scratch (3 facet_dofs x n_cell x nrhs), the static scratch holds " +
                                         std::to_string(NOALLOC_SCRATCH_DOUBLES) + ": use hdg_condense"};
         HDG_REQUIRE(c->noalloc_scratch, "static scratch not resolved for this device");
-        hdg::launch_condense(c->p, c->nu, c->n_cell, c->n_facet, nb, c->Zr, r_cell, c->noalloc_scratch, c->d_fcell,
-                             c->d_floc, rhat, as_stream(stream), c->cell_cells);
+        condense(c, nb, r_cell, c->noalloc_scratch, rhat, as_stream(stream), c->cell_cells);
         check_launch();
     });
 }
@@ -1731,13 +1774,11 @@ extern "C" int hdg_stage_solve(hdg_ctx *c, int32_t nb, const double *r_cell, dou
             status = solve_small(c, nb, kry, true, nullptr, r_cell, lam, q_cell, info, s);
             return;
         }
-        hdg::launch_condense(c->p, c->nu, c->n_cell, c->n_facet, nb, c->Zr, r_cell, c->loc, c->d_fcell, c->d_floc,
-                             c->stage_rhat, s, c->cell_cells);
+        condense(c, nb, r_cell, c->loc, c->stage_rhat, s, c->cell_cells);
         check_launch();
         HDG_HIP_CHECK(hipMemsetAsync(lam, 0, sizeof(double) * (size_t)vec_len(c) * nb, s));
         status = solve_impl(c, nb, c->stage_rhat, lam, info, s);
-        hdg::launch_recover(c->p, c->nu, c->n_cell, nb, c->Ar, c->Wr, c->cell_facet, c->cell_rev, r_cell, lam, q_cell,
-                            s, c->cell_cells);
+        recover(c, nb, r_cell, lam, q_cell, s, c->cell_cells);
         check_launch();
         HDG_HIP_CHECK(hipStreamSynchronize(s));
     });
@@ -1756,8 +1797,7 @@ extern "C" int hdg_recover(hdg_ctx *c, int32_t nb, const double *r_cell, const d
         hipStream_t s = as_stream(stream);
         Timed t(c, HDG_KERNEL_RECOVER, HDG_FP64, s, nb);
         for (int rep = 0; rep < t.repeats(); ++rep)
-            hdg::launch_recover(c->p, c->nu, c->n_cell, nb, c->Ar, c->Wr, c->cell_facet, c->cell_rev, r_cell, lam, q_cell,
-                                s, c->cell_cells);
+            recover(c, nb, r_cell, lam, q_cell, s, c->cell_cells);
         check_launch();
     });
 }
@@ -2051,7 +2091,7 @@ extern "C" int hdg_autotune(hdg_ctx *c, int32_t nb, hdg_tuning *chosen, void *st
         // batched cell kernels (condensation, recovery): the most cells per block
         // that fit, half or a quarter of them
         int best_cc = 0;
-        if (nb >= 2) {
+        if (nb >= 2 && (c->flux == HDG_FLUX_LF || c->cf.zt)) {
             const size_t cell_bytes = sizeof(double) * (size_t)c->n_cell * c->nc * nb;
             struct Scratch {   // freed on every way out, errors included
                 double *p = nullptr;
@@ -2068,10 +2108,8 @@ extern "C" int hdg_autotune(hdg_ctx *c, int32_t nb, hdg_tuning *chosen, void *st
                 const int mx = std::max(1, std::min(32, 256 / nb));   // upper bound; the launcher clamps further
                 const int cc = div == 1 ? 0 : std::max(1, mx / div);
                 const double ms = time_launches(s, 5, [&] {
-                    hdg::launch_condense(c->p, c->nu, c->n_cell, c->n_facet, nb, c->Zr, rc, c->loc, c->d_fcell,
-                                         c->d_floc, c->vres, s, cc);
-                    hdg::launch_recover(c->p, c->nu, c->n_cell, nb, c->Ar, c->Wr, c->cell_facet, c->cell_rev, rc,
-                                        c->vx, qc, s, cc);
+                    condense(c, nb, rc, c->loc, c->vres, s, cc);
+                    recover(c, nb, rc, c->vx, qc, s, cc);
                 });
                 if (ms < best) {
                     best = ms;
@@ -2121,13 +2159,18 @@ extern "C" int hdg_kernel_stats(hdg_ctx *c, int32_t kernel, int32_t prec, int64_
             // vector entry sizes of the timed launches (FP32 vectors inside mixed solves)
             const double sx = c->t_sx[prec][kernel] ? c->t_sx[prec][kernel] : 8;
             const double sy = c->t_sy[prec][kernel] ? c->t_sy[prec][kernel] : 8;
+            // a cell's stored numbers: the dense maps (Lax-Friedrichs) or the cell-pass factors
+            const bool lf = c->flux == HDG_FLUX_LF;
+            const double n2 = (double)c->n * c->n, cf = hdg::CELL_GEO + (c->cf.zt ? 5 * n2 : n2);
             double b = 0;
             switch (kernel) {
             case HDG_KERNEL_APPLY: b = ne * (5 * m * m * sm + 4 * 4) + nb * ne * m * (sx + sy); break;
             case HDG_KERNEL_RESIDUAL: b = ne * (5 * m * m * sm + 4 * 4) + nb * ne * m * (sx + 2 * sy); break;
             case HDG_KERNEL_SWEEP: b = ne * (4 * m * m * st + 4 * 4) + nb * ne * 3 * m * sx; break;
-            case HDG_KERNEL_CONDENSE: b = nk * nt * nc * 8 + nb * (nk * nc * 8 + ne * m * 8); break;
-            case HDG_KERNEL_RECOVER: b = nk * (nc * nc + nc * nt) * 8 + nb * (nk * 2 * nc * 8 + ne * m * 8); break;
+            case HDG_KERNEL_CONDENSE: b = nk * (lf || c->cf.zt ? nt * nc : cf) * 8 + nb * (nk * nc * 8 + ne * m * 8); break;
+            case HDG_KERNEL_RECOVER:
+                b = nk * (lf ? nc * nc + nc * nt : cf) * 8 + nb * (nk * 2 * nc * 8 + ne * m * 8);
+                break;
             case HDG_KERNEL_MLP: b = ne * (4 * 4 + 4) + nb * ne * 3 * m * sx; break;
             }
             // launches that stated their own bytes (operands that alias counted once, optional

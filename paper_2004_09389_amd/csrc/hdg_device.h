@@ -86,4 +86,19 @@ __device__ __forceinline__ double acc_row(double init, int cnt, F &&f) {
     return s;
 }
 
+// cnt contiguous values of the block's cells <-> LDS, eight loads per thread in flight
+__device__ __forceinline__ void stage_cells(const double *__restrict__ src, double *__restrict__ dst, int cnt) {
+    constexpr int U = 8;
+    const int step = blockDim.x;
+    for (int i0 = threadIdx.x; i0 < cnt; i0 += U * step) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * step < cnt) v[u] = src[i0 + u * step];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * step < cnt) dst[i0 + u * step] = v[u];
+    }
+}
+
 }  // namespace hdg

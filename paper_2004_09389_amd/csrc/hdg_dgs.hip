@@ -587,8 +587,8 @@ extern "C" int hdg_dgs_setup(hdg_ctx *c, const hdg_mesh *levels, int32_t n_level
         HDG_HIP_CHECK(hipMemset(d_err, 0, sizeof(int)));
         hipStream_t s = nullptr;
         hdg::CellParams cp{c->kappa, c->tau, c->dt, c->prm.f0, c->prm.omega, c->hscale, c->geom};
-        hdg::launch_cell_condense(c->p, 1, nk, c->corners, c->ref, cp, nullptr, nullptr, nullptr, nullptr, d_err, s,
-                                  c->dgs_A, c->dgs_Bn);
+        hdg::launch_cell_condense(c->p, 1, nk, c->corners, c->ref, cp, nullptr, nullptr, nullptr, nullptr, nullptr, false, nullptr,
+                                  d_err, s, c->dgs_A, c->dgs_Bn);
         hdg::check_kernel_launch();
 #define LOCAL(P)                                                                                                   \
     hipLaunchKernelGGL(hdg::k_dgs_local<P>, dim3(nk), dim3(64), 0, s, nk, c->geom, c->tau, c->corners, c->dgs_A, \

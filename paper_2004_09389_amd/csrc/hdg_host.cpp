@@ -281,6 +281,32 @@ RefTables build_ref_tables(int p) {
     return R;
 }
 
+std::vector<double> cell_tables(const RefTables &R) {
+    const int n = R.n, m = R.m;
+    std::vector<double> Mi = R.M;
+    if (!invert_dense(Mi, n)) throw Error{HDG_EINVAL, "singular reference mass matrix"};
+    std::vector<double> t;
+    // M^-1 times an n x w table, entry (j, k) at a[j * sj + k * sk]; tr: its transpose
+    auto mul = [&](const double *a, int w, int sj, int sk, bool tr) {
+        const size_t o = t.size();
+        t.resize(o + (size_t)n * w);
+        for (int i = 0; i < n; ++i)
+            for (int k = 0; k < w; ++k) {
+                double v = 0.0;
+                for (int j = 0; j < n; ++j) v += Mi[(size_t)i * n + j] * a[(size_t)j * sj + (size_t)k * sk];
+                t[o + (tr ? (size_t)k * n + i : (size_t)i * w + k)] = v;
+            }
+    };
+    for (int r = 0; r < 2; ++r) mul(&R.G[(size_t)r * n * n], n, n, 1, true);
+    for (int r = 0; r < 2; ++r) mul(&R.G[(size_t)r * n * n], n, 1, n, true);
+    for (int f = 0; f < 3; ++f) mul(&R.T[(size_t)f * n * m], m, m, 1, false);
+    t.insert(t.end(), R.F.begin(), R.F.end());
+    t.insert(t.end(), Mi.begin(), Mi.end());
+    t.insert(t.end(), R.qw.begin(), R.qw.end());
+    t.insert(t.end(), R.Phi.begin(), R.Phi.end());
+    return t;
+}
+
 // ------------------------------------------------------------------ P1 levels
 //
 // Coarse form of the upwind case (Eq. coarse_problem_upwind) scaled to the

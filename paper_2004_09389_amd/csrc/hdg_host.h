@@ -55,6 +55,9 @@ struct RefTables {
     std::vector<double> Phi;   // [nq][n]     basis values at the points
 };
 RefTables build_ref_tables(int p);
+// the tables of the upwind cell passes: D [2][n][n] = (M^-1 G_r)^T, K [2][n][n] = (M^-1 G_r^T)^T,
+// X [3][n][m] = M^-1 T_f, F [m][m], M^-1 [n][n], the quadrature weights [nq] and basis values [nq][n]
+std::vector<double> cell_tables(const RefTables &R);
 
 // ------------------------------------------------------------------ P1 levels (host)
 struct P1Host {

@@ -18,7 +18,7 @@
 #include <string>
 #include <vector>
 
-#include "hdg_internal.h"
+#include "hdg_kernels.h"
 
 namespace hdg {
 namespace {
@@ -266,6 +266,14 @@ double *half_buffer(hdg_ctx *c) {
 
 void dg_tendency(hdg_ctx *c, int nb, double dt, const double *q, double *out, hipStream_t s) {
     double *half = half_buffer(c);
+    const double scale = dt / c->dt;
+    launch_dg_half(c, nb, c->hscale, q, half, s);
+    if (c->nu == 1) {
+        launch_cell_tendency(c->p, c->n_cell, nb, c->cf, scale, c->dt, c->prm.f0, c->prm.omega, c->corners, c->qx,
+                             c->cell_facet, c->cell_rev, q, half, out, s);
+        check_kernel_launch();
+        return;
+    }
     int *err = c->dg_err;
     if (!err) {
         void *p = nullptr;
@@ -275,33 +283,21 @@ void dg_tendency(hdg_ctx *c, int nb, double dt, const double *q, double *out, hi
         c->dg_err = err = static_cast<int *>(p);
     }
     HDG_HIP_CHECK(hipMemsetAsync(err, 0, sizeof(int), s));
-    const int64_t nth = (int64_t)c->n_cell * 3 * nb;
-    const int block = 256;
-    const unsigned grid = (unsigned)((nth + block - 1) / block);
-    const double scale = dt / c->dt;
-#define HALF(P, NU)                                                                                              \
-    hipLaunchKernelGGL((k_dg_half<P, NU>), dim3(grid), dim3(block), 0, s, c->n_cell, nb, c->geom, c->tau, c->hscale, \
-                       c->corners, c->cell_facet, c->cell_rev, q, half)
     const size_t lds = (size_t)(c->nc * (c->nc + nb) + c->nt * nb + c->nc) * sizeof(double);
-#define TEND(P, NU)                                                                                               \
-    hipLaunchKernelGGL((k_dg_tendency<P, NU>), dim3(c->n_cell), dim3(64), lds, s, c->n_cell, nb, scale, c->Ar, c->Wr, \
+#define TEND(P)                                                                                                   \
+    hipLaunchKernelGGL((k_dg_tendency<P, 2>), dim3(c->n_cell), dim3(64), lds, s, c->n_cell, nb, scale, c->Ar, c->Wr, \
                        c->cell_facet, c->cell_rev, q, half, out, err)
-    if (c->nu == 1) {
-        switch (c->p) {
-            case 1: HALF(1, 1); check_kernel_launch(); TEND(1, 1); break;
-            case 2: HALF(2, 1); check_kernel_launch(); TEND(2, 1); break;
-            default: HALF(3, 1); check_kernel_launch(); TEND(3, 1); break;
-        }
-    } else {
-        switch (c->p) {
-            case 1: HALF(1, 2); check_kernel_launch(); TEND(1, 2); break;
-            case 2: HALF(2, 2); check_kernel_launch(); TEND(2, 2); break;
-            default: HALF(3, 2); check_kernel_launch(); TEND(3, 2); break;
-        }
+    switch (c->p) {
+        case 1: TEND(1); break;
+        case 2: TEND(2); break;
+        default: TEND(3); break;
     }
-#undef HALF
 #undef TEND
     check_kernel_launch();
+    int herr = 0;
+    HDG_HIP_CHECK(hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, s));
+    HDG_HIP_CHECK(hipStreamSynchronize(s));
+    if (herr) throw Error{HDG_EBREAKDOWN, "singular recovery matrix in the flux evaluation"};
 }
 
 struct Plan {
@@ -472,10 +468,6 @@ extern "C" int hdg_dg_tendency(hdg_ctx *c, int32_t nb, double dt, const double *
         HDG_REQUIRE(std::isfinite(dt), "dt must be finite");
         hipStream_t s = reinterpret_cast<hipStream_t>(stream);
         hdg::dg_tendency(c, nb, dt, q, out, s);
-        int herr = 0;
-        HDG_HIP_CHECK(hipMemcpyAsync(&herr, c->dg_err, sizeof(int), hipMemcpyDeviceToHost, s));
-        HDG_HIP_CHECK(hipStreamSynchronize(s));
-        if (herr) throw Error{HDG_EBREAKDOWN, "singular recovery matrix in the flux evaluation"};
     });
 }
 
@@ -517,10 +509,6 @@ extern "C" int hdg_imex_run(hdg_ctx *c, const hdg_imex_tableau *tab, double dt, 
         for (int step = 0; step < steps; ++step) {
             if (pl.need_tend && (step == 0 || !pl.fsal)) {
                 hdg::dg_tendency(c, nb, dt, q, tend, st);
-                int herr = 0;
-                HDG_HIP_CHECK(hipMemcpyAsync(&herr, c->dg_err, sizeof(int), hipMemcpyDeviceToHost, st));
-                HDG_HIP_CHECK(hipStreamSynchronize(st));
-                if (herr) throw Error{HDG_EBREAKDOWN, "singular recovery matrix in the flux evaluation"};
             }
             for (int i = 0; i < s; ++i) {
                 if (i == 0 && at[0][0] == 0.0) {

@@ -81,6 +81,15 @@ struct P1Dense {
     int top = 0;
 };
 
+// Factors of the upwind cell passes (hdg_cells.hip).  Per cell, 16-byte pairs [pair][n_cell]:
+// geo: 14 factors of the affine map; tab: cell_tables.  f uniform: fs = Sigma^-1 M [n][n] (padded
+// to an even count), Z = za + i zb; f varying inside the cells (zt non-null): fs = the depth rows
+// of A^-1 M [n][3 n, padded even], zt = Z [n][n] complex.
+struct CellFactors {
+    const double *geo = nullptr, *fs = nullptr, *zt = nullptr, *tab = nullptr;
+    double za = 1.0, zb = 0.0, hs = 1.0;
+};
+
 // RT0 level on the device (Lax-Friedrichs coarse space), arrays as in Rt0Host
 struct Rt0LevelDev {
     int ne = 0, nv = 0;
@@ -136,7 +145,10 @@ struct hdg_ctx {
     int64_t device_bytes = 0;
     std::vector<void *> allocations;
 
-    // per-cell matrices, component-major [row][col][n_cell]
+    // factors of the upwind cell passes (condensation, recovery, explicit flux evaluation)
+    hdg::CellFactors cf;
+    const double *qx = nullptr;     // the setup's quadrature points [nq][2]
+    // dense cell maps, component-major [row][col][n_cell]: Lax-Friedrichs, and the single-launch solve
     double *Zr = nullptr;      // [nt][nc, padded even]  C A^-1 Mtilde  (condense), 16-byte pairs
     double *Ar = nullptr;      // [nc][nc]  A^-1 Mtilde, phi rows / hscale  (recover)
     double *Wr = nullptr;      // [nc][nt]  A^-1 B, phi rows / hscale       (recover)
@@ -144,7 +156,7 @@ struct hdg_ctx {
     int8_t *cell_rev = nullptr;     // [3][n_cell]
     double *corners = nullptr;      // [n_cell][3][3] unwrapped corner coordinates
     double *dg_half = nullptr;      // explicit flux evaluation: trace shares [n_facet][2][m][max_rhs]
-    int *dg_err = nullptr;          // its singular-matrix flag
+    int *dg_err = nullptr;          // its singular-matrix flag (Lax-Friedrichs)
     double *ref = nullptr;          // reference-element tables of the cell assembly
 
     // non-hybridised DG baseline (hdg_dgs_setup): stage matrix as A q + B lam(q) per cell

@@ -134,12 +134,26 @@ struct CellParams {
     int geom;
 };
 
+constexpr int CELL_GEO = 14;
+constexpr int CELL_SMALL_RHS = 8;   // right-hand sides up to which a block's cell vectors go through LDS
+// recovery (out = q); uniform f also the cell part of the condensation (out = loc [nt][n_cell][nb], lam unused)
+void launch_cell_pass(int p, bool rec, int nk, int nb, const CellFactors &c, const int *cell_facet,
+                      const int8_t *cell_rev, const double *rc, const double *lam, double *out, hipStream_t s);
+// out = scale (q - r), r the right-hand side of the stage equations with q and the trace half[0] + half[1]
+void launch_cell_tendency(int p, int nk, int nb, const CellFactors &c, double scale, double dt, double f0, double omega,
+                          const double *corners, const double *qx, const int *cell_facet, const int8_t *cell_rev,
+                          const double *q, const double *half, double *out, hipStream_t s);
+void launch_cell_rot(int p, int nk, const double *corners, const double *ref_M, const double *qx, const double *tab,
+                     double dt, double f0, double omega, double *zt, hipStream_t s);
+
 // nu: trace components per node (1 upwind, 2 Lax-Friedrichs)
+// Zr; Ar, Wr: the dense maps (null: not stored).  fs (its depth rows where
+// fs_rows), geo (upwind): the cell-pass factors.
 // With Aout non-null the kernel only assembles and stores A_K ([nc][nc][nk]) and -B_K
 // ([nc][nt][nk], into Bnout), skipping the condensation.
 void launch_cell_condense(int p, int nu, int nk, const double *corners, const double *ref, CellParams cp,
-                          double *Sloc, double *Zr, double *Ar, double *Wr, int *err, hipStream_t s,
-                          double *Aout = nullptr, double *Bnout = nullptr);
+                          double *Sloc, double *Zr, double *Ar, double *Wr, double *fs, bool fs_rows, double *geo, int *err,
+                          hipStream_t s, double *Aout = nullptr, double *Bnout = nullptr);
 void launch_facet_rows(int p, int nu, int ne, int nk, const double *Sloc, const int *facet_cell,
                        const int *facet_loc, const int *cell_facet, const int8_t *cell_rev, double omega,
                        double *S64, double *T64, double *Dw64, float *S32, __hip_bfloat16 *T16, float *Dw32,
@@ -198,10 +212,15 @@ size_t dense_doubles(int n);                    // entries of B, padding include
 void launch_dense_cols(int n, int col0, int ncol, const double *src, double *B, hipStream_t s);
 void launch_unit_cols(int n, int col0, int ncol, double *b, hipStream_t s);
 
-// cells: cells per block of the batched (nb >= 2) cell kernels; 0 = the most
-// that fit (256 threads, 64 KiB of staged rows), larger requests are clamped
-void launch_condense(int p, int nu, int nk, int ne, int nb, const double *Zr, const double *rc, double *loc,
-                     const int *facet_cell, const int *facet_loc, double *rhat, hipStream_t s, int cells = 0);
+// Cell passes by dense maps: condensation of the Lax-Friedrichs form and of the upwind form
+// where f varies inside the cells; recovery of the Lax-Friedrichs form and the DG baseline's
+// stage operator.  cells: cells per block of the batched (staged-row) kernels; 0 =
+// the most that fit (256 threads, 64 KiB of staged rows), larger requests are clamped.
+void launch_condense_cell(int p, int nu, int nk, int nb, const double *Zr, const double *rc, double *loc,
+                          hipStream_t s, int cells = 0);
+// rhat from the cells' contributions loc [nt][n_cell][nb]
+void launch_condense_gather(int p, int nu, int nk, int ne, int nb, const double *loc, const int *facet_cell,
+                            const int *facet_loc, double *rhat, hipStream_t s);
 void launch_recover(int p, int nu, int nk, int nb, const double *Ar, const double *Wr, const int *cell_facet,
                     const int8_t *cell_rev, const double *rc, const double *lam, double *q, hipStream_t s,
                     int cells = 0);

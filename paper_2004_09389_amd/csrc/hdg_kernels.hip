@@ -61,6 +61,7 @@ __global__ __launch_bounds__(64) void k_cell_condense(int nk, const double *__re
                                                       const double *__restrict__ ref, CellParams cp,
                                                       double *__restrict__ Sloc, double *__restrict__ Zr,
                                                       double *__restrict__ Ar, double *__restrict__ Wr,
+                                                      double *__restrict__ fs, bool fs_rows, double *__restrict__ geo,
                                                       int *__restrict__ err, double *__restrict__ Aout,
                                                       double *__restrict__ Bnout) {
     constexpr int n = (P + 1) * (P + 2) / 2, m = P + 1, nc = 3 * n, M = NU * m, nt = 3 * M, nq = (P + 3) * (P + 3);
@@ -291,7 +292,31 @@ __global__ __launch_bounds__(64) void k_cell_condense(int nk, const double *__re
     // depth unknown) from the registers, then S_K = Mt + C W and C A^-1 Mtilde
     // from the solution staged through LDS a round of columns at a time
     const double ih = 1.0 / cp.hscale;
-    if (ok && myk >= 0) {
+    if constexpr (NU == 1) {
+        // the factors of the cell passes: Sigma^-1 M is the depth block of A^-1 Mtilde (fs_rows: its depth rows, padded to pairs)
+        if (fs && ok && myk >= 0 && myk < n) {
+#pragma unroll
+            for (int b = 0; b < nc; ++b) {
+                if (b >= (fs_rows ? nc : n)) break;
+                const int idx = fs_rows ? myk * ((nc + 1) / 2 * 2) + b : myk * n + b;
+                fs[((size_t)(idx / 2) * NK + K) * 2 + idx % 2] = (b < n ? ih : 1.0) * (myip * a[nc + nt + b]);
+            }
+            if (fs_rows ? nc % 2 != 0 : n * n % 2 && myk == 0) {   // the padding entry
+                const int idx = fs_rows ? myk * (nc + 1) + nc : n * n;
+                fs[((size_t)(idx / 2) * NK + K) * 2 + idx % 2] = 0.0;
+            }
+        }
+        if (geo && ok && r == 0) {
+            const double kd = kap / det;
+            const double v[CELL_GEO] = {kap * J00, kap * J01, kap * J10, kap * J11,
+                                        kd * L[0] * nx[0], kd * L[0] * ny[0], kd * L[1] * nx[1], kd * L[1] * ny[1],
+                                        kd * L[2] * nx[2], kd * L[2] * ny[2], kd * tau * L[0], kd * tau * L[1],
+                                        kd * tau * L[2], det / kap};
+#pragma unroll
+            for (int q = 0; q < CELL_GEO; ++q) geo[((size_t)(q / 2) * NK + K) * 2 + q % 2] = v[q];
+        }
+    }
+    if (Ar && ok && myk >= 0) {
         const double sc = myk < n ? ih : 1.0;
 #pragma unroll
         for (int b = 0; b < nc; ++b) Ar[(size_t)(myk * nc + b) * NK + K] = sc * (myip * a[nc + nt + b]);
@@ -301,6 +326,7 @@ __global__ __launch_bounds__(64) void k_cell_condense(int nk, const double *__re
 #pragma unroll
     for (int rho = 0; rho < NR; ++rho) {
         const int lo = rho * XB, hi = lo + XB < NX ? lo + XB : NX;
+        if (lo >= nt && !Zr) break;   // the remaining columns are C A^-1 Mtilde alone
         __syncthreads();
         if (myk >= 0) {
 #pragma unroll
@@ -319,7 +345,7 @@ __global__ __launch_bounds__(64) void k_cell_condense(int nk, const double *__re
                 Sloc[(size_t)(aa * nt + b) * NK + K] = s;
             }
         }
-        if (hi > nt) {   // C A^-1 Mtilde columns [max(lo, nt), hi) - nt, rows padded to ZW, 16-byte pairs
+        if (hi > nt && Zr) {   // C A^-1 Mtilde columns [max(lo, nt), hi) - nt, rows padded to ZW, 16-byte pairs
             const int x0 = lo > nt ? lo : nt, w = hi - x0;
             for (int t = r; t < nt * w; t += 32) {
                 const int aa = t / w, b = x0 - nt + t % w;
@@ -331,7 +357,7 @@ __global__ __launch_bounds__(64) void k_cell_condense(int nk, const double *__re
         }
     }
     if constexpr (ZW > nc) {
-        for (int t = r; ok && t < nt * (ZW - nc); t += 32) {
+        for (int t = r; ok && Zr && t < nt * (ZW - nc); t += 32) {
             const int idx = (t / (ZW - nc)) * ZW + nc + t % (ZW - nc);
             Zr[((size_t)(idx / 2) * NK + K) * 2 + idx % 2] = 0.0;
         }
@@ -807,26 +833,39 @@ __global__ void k_p1_restrict(int nc, int nb, const int *__restrict__ crow, cons
 // ------------------------------------------------------------------ condensation / recovery (per solve)
 
 // loc[rho][K][r] = sum_j Zr[rho][j][K] r_cell[K][j][r]   (Step 1, cell part)
-constexpr int RECOVER_TILE = 128;   // cells per block of the one-right-hand-side cell kernels
+constexpr int RECOVER_TILE = 128;   // threads per block of the small-batch cell kernels
+// Up to this many right-hand sides at degree p the dense maps are read per thread; above, staged
+// rows serve a whole batch.  Condensation on the level-6 sphere, per thread / staged: p = 3 at
+// 2, 4, 8 right-hand sides 57 / 376, 77 / 227, 126 / 175 us; p = 2 at 4, 5, 6, 8
+// 43 / 56, 54 / 55, 58 / 54, 70 / 63 us; p = 1 at 4, 6, 8 23 / 22, 30 / 25, 38 / 29 us.
+__host__ __device__ constexpr int cell_small_dense(int p) { return p == 3 ? 8 : (p == 2 ? 5 : 3); }
 
-// Condensation at one right-hand side: the block's cells read their inputs
-// through LDS (coalesced global loads).  NU trace components per node (1:
-// upwind, 2: Lax-Friedrichs).
-template <int P, int NU>
-__global__ __launch_bounds__(RECOVER_TILE) void k_condense_cell_n1(int nk, const double *__restrict__ Zr,
-                                                                  const double *__restrict__ rc,
-                                                                  double *__restrict__ loc) {
+// Condensation by the dense map at up to cell_small_dense(P) right-hand sides: one thread per
+// (cell, right-hand side), right-hand side fastest.  The block's cells read their inputs
+// through LDS (coalesced), the map's 16-byte pairs come
+// straight from memory: lanes of one cell share an address, consecutive cells are
+// consecutive, so a wavefront's load is one contiguous piece.  Held to three wavefronts
+// per SIMD (what the LDS allows at p = 3 anyway): the compiler then spends the registers
+// on loads in flight (level-6 sphere, p = 3, one right-hand side: 54 us, 94 without).
+// NU trace components per node (1: upwind, 2: Lax-Friedrichs).
+template <int P, int NU, bool NB1>
+__global__ __launch_bounds__(RECOVER_TILE) __attribute__((amdgpu_waves_per_eu(2, 3))) void k_condense_cell_s(int nk, int nrhs, const double *__restrict__ Zr,
+                                                                 const double *__restrict__ rc,
+                                                                 double *__restrict__ loc) {
     constexpr int n = (P + 1) * (P + 2) / 2, m = P + 1, nc = 3 * n, nt = 3 * NU * m, ZW = cell_zw(P);
-    __shared__ double buf[RECOVER_TILE * nc];
-    const int K0 = xcd_block() * RECOVER_TILE, tid = threadIdx.x, K = K0 + tid;
-    const int cnt = min(RECOVER_TILE, nk - K0);
+    extern __shared__ double buf[];
+    const int nb = NB1 ? 1 : nrhs;
+    const int cpb = RECOVER_TILE / nb, per = nc * nb;
+    const int K0 = xcd_block() * cpb, tid = threadIdx.x, cl = tid / nb, r = tid - cl * nb, K = K0 + cl;
+    const int cnt = min(cpb, nk - K0);   // may be <= 0 in the padding blocks
     const size_t NK = (size_t)nk;
-    for (int i = tid; i < cnt * nc; i += RECOVER_TILE) buf[i] = rc[(size_t)K0 * nc + i];
+    if (cnt <= 0) return;   // the whole block
+    stage_cells(rc + (size_t)K0 * per, buf, cnt * per);
     __syncthreads();
-    if (tid >= cnt) return;
+    if (cl >= cnt) return;
     double f[ZW];
 #pragma unroll
-    for (int j = 0; j < ZW; ++j) f[j] = j < nc ? buf[tid * nc + j] : 0.0;
+    for (int j = 0; j < ZW; ++j) f[j] = j < nc ? buf[cl * per + j * nb + r] : 0.0;
 #pragma unroll
     for (int a = 0; a < nt; ++a) {
         double s = 0.0;
@@ -837,7 +876,7 @@ __global__ __launch_bounds__(RECOVER_TILE) void k_condense_cell_n1(int nk, const
             s += w[0] * f[2 * jp];
             if (2 * jp + 1 < nc) s += w[1] * f[2 * jp + 1];
         }
-        loc[(size_t)a * NK + K] = s;
+        loc[((size_t)a * NK + K) * nb + r] = s;
     }
 }
 
@@ -858,38 +897,38 @@ __global__ void k_condense_gather(int ne, int nk, int nb, const int *__restrict_
     rhat[t] = v0 + v1;
 }
 
-// Recovery q = Ar r_cell - Wr lam_K (Step 3) with one right-hand side: the
-// block's cells read their inputs and write their outputs through LDS, so the
-// global traffic of r_cell and q (nc consecutive values per cell) is coalesced.
-template <int P, int NU>
-__global__ __launch_bounds__(RECOVER_TILE) void k_recover_n1(int nk, const double *__restrict__ Ar,
-                                                            const double *__restrict__ Wr,
-                                                            const int *__restrict__ cell_facet,
-                                                            const int8_t *__restrict__ cell_rev,
-                                                            const double *__restrict__ rc,
-                                                            const double *__restrict__ lam, double *__restrict__ q) {
+// Recovery q = Ar r_cell - Wr lam_K (Step 3) by the dense maps at up to cell_small_dense(P)
+// right-hand sides, threads and staging as above (outputs too go through LDS).
+template <int P, int NU, bool NB1>
+__global__ __launch_bounds__(RECOVER_TILE) __attribute__((amdgpu_waves_per_eu(2, 3))) void k_recover_s(int nk, int nrhs, const double *__restrict__ Ar,
+                                                           const double *__restrict__ Wr,
+                                                           const int *__restrict__ cell_facet,
+                                                           const int8_t *__restrict__ cell_rev,
+                                                           const double *__restrict__ rc,
+                                                           const double *__restrict__ lam, double *__restrict__ q) {
     constexpr int n = (P + 1) * (P + 2) / 2, m = P + 1, nc = 3 * n, M = NU * m, nt = 3 * M;
-    __shared__ double buf[RECOVER_TILE * nc];
-    const int K0 = xcd_block() * RECOVER_TILE, tid = threadIdx.x, K = K0 + tid;
-    const int cnt = min(RECOVER_TILE, nk - K0);   // may be <= 0 in the padding blocks
+    extern __shared__ double buf[];
+    const int nb = NB1 ? 1 : nrhs;
+    const int cpb = RECOVER_TILE / nb, per = nc * nb;
+    const int K0 = xcd_block() * cpb, tid = threadIdx.x, cl = tid / nb, r = tid - cl * nb, K = K0 + cl;
+    const int cnt = min(cpb, nk - K0);   // may be <= 0 in the padding blocks
     const size_t NK = (size_t)nk;
-    for (int i = tid; i < cnt * nc; i += RECOVER_TILE) buf[i] = rc[(size_t)K0 * nc + i];
+    if (cnt <= 0) return;   // the whole block
+    stage_cells(rc + (size_t)K0 * per, buf, cnt * per);
     __syncthreads();
     double f[nc], l[nt];
-    const bool live = tid < cnt;
+    const bool live = cl < cnt;
+    double *mine = buf + cl * per + r;
 #pragma unroll
-    for (int j = 0; j < nc; ++j) f[j] = live ? buf[tid * nc + j] : 0.0;
+    for (int j = 0; j < nc; ++j) f[j] = live ? mine[j * nb] : 0.0;
     if (live) {
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             const int e = cell_facet[i * NK + K];
             const int rev = cell_rev[i * NK + K];
 #pragma unroll
-            for (int a = 0; a < M; ++a) l[loc_trace<P, NU>(i, a, rev)] = lam[(size_t)e * M + a];
+            for (int a = 0; a < M; ++a) l[loc_trace<P, NU>(i, a, rev)] = lam[((size_t)e * M + a) * nb + r];
         }
-    }
-    __syncthreads();
-    if (live) {
 #pragma unroll 1
         for (int a = 0; a < nc; ++a) {
             double s = 0.0;
@@ -897,14 +936,14 @@ __global__ __launch_bounds__(RECOVER_TILE) void k_recover_n1(int nk, const doubl
             for (int j = 0; j < nc; ++j) s += ldm(Ar + (size_t)(a * nc + j) * NK + K) * f[j];
 #pragma unroll
             for (int j = 0; j < nt; ++j) s -= ldm(Wr + (size_t)(a * nt + j) * NK + K) * l[j];
-            buf[tid * nc + a] = s;
+            mine[a * nb] = s;
         }
     }
     __syncthreads();
-    for (int i = tid; i < cnt * nc; i += RECOVER_TILE) q[(size_t)K0 * nc + i] = buf[i];
+    stage_cells(buf, q + (size_t)K0 * per, cnt * per);
 }
 
-// Batched cell kernels (nrhs >= 2): a block holds CB cells x nrhs threads
+// Batched cell kernels (more than cell_small_dense(P) right-hand sides): a block holds CB cells x nrhs threads
 // (right-hand side fastest) and streams the cells' matrix rows through LDS in
 // chunks of CELL_ROWS rows, loaded once per block with coalesced reads; every
 // thread keeps its right-hand side's inputs in registers.  Same arithmetic
@@ -2081,10 +2120,10 @@ bool rhs_blocked(int nb, int rhs_block) {
 #define GRID8(n, b) dim3((unsigned)((((n) + (b) - 1) / (b) + N_XCD - 1) / N_XCD * N_XCD)), dim3(b)
 
 void launch_cell_condense(int p, int nu, int nk, const double *corners, const double *ref, CellParams cp,
-                          double *Sloc, double *Zr, double *Ar, double *Wr, int *err, hipStream_t s, double *Aout,
-                          double *Bnout) {
+                          double *Sloc, double *Zr, double *Ar, double *Wr, double *fs, bool fs_rows, double *geo, int *err,
+                          hipStream_t s, double *Aout, double *Bnout) {
     const int pairs = (nk + 1) / 2;   // two cells per wavefront
-#define CK(P, NU) hipLaunchKernelGGL((k_cell_condense<P, NU>), dim3((unsigned)((pairs + N_XCD - 1) / N_XCD * N_XCD)), dim3(64), 0, s, nk, corners, ref, cp, Sloc, Zr, Ar, Wr, err, Aout, Bnout)
+#define CK(P, NU) hipLaunchKernelGGL((k_cell_condense<P, NU>), dim3((unsigned)((pairs + N_XCD - 1) / N_XCD * N_XCD)), dim3(64), 0, s, nk, corners, ref, cp, Sloc, Zr, Ar, Wr, fs, fs_rows, geo, err, Aout, Bnout)
     if (nu == 1) { switch (p) { case 1: CK(1, 1); break; case 2: CK(2, 1); break; case 3: CK(3, 1); break; } }
     else { switch (p) { case 1: CK(1, 2); break; case 2: CK(2, 2); break; case 3: CK(3, 2); break; } }
 #undef CK
@@ -2312,20 +2351,36 @@ void launch_unit_cols(int n, int col0, int ncol, double *b, hipStream_t s) {
 }
 #undef P1_TYPED
 
-void launch_condense(int p, int nu, int nk, int ne, int nb, const double *Zr, const double *rc, double *loc,
-                     const int *facet_cell, const int *facet_loc, double *rhat, hipStream_t s, int cells) {
+// small batches: dynamic LDS of a block's cell vectors
+static dim3 cell_grid(int nk, int nb) {
+    const int cpb = RECOVER_TILE / nb;
+    return dim3((unsigned)(((nk + cpb - 1) / cpb + N_XCD - 1) / N_XCD * N_XCD));
+}
+static size_t small_bytes(int nc, int nb) { return sizeof(double) * (RECOVER_TILE / nb) * nc * nb; }
+void launch_condense_cell(int p, int nu, int nk, int nb, const double *Zr, const double *rc, double *loc,
+                          hipStream_t s, int cells) {
 #define CC(P, NU)                                                                                                 \
     if (nb == 1)                                                                                                  \
-        hipLaunchKernelGGL((k_condense_cell_n1<P, NU>), GRID8(nk, RECOVER_TILE), 0, s, nk, Zr, rc, loc);          \
+        hipLaunchKernelGGL((k_condense_cell_s<P, NU, true>), cell_grid(nk, nb), dim3(RECOVER_TILE),               \
+                           small_bytes(3 * (P + 1) * (P + 2) / 2, nb), s, nk, nb, Zr, rc, loc);                   \
+    else if (nb <= cell_small_dense(P))                                                                              \
+        hipLaunchKernelGGL((k_condense_cell_s<P, NU, false>), cell_grid(nk, nb), dim3(RECOVER_TILE),              \
+                           small_bytes(3 * (P + 1) * (P + 2) / 2, nb), s, nk, nb, Zr, rc, loc);                   \
     else                                                                                                          \
         hipLaunchKernelGGL((k_condense_cell_b<P, NU>), GRID8((int64_t)nk * nb, cell_cells(nb, cell_zw(P), cells) * nb), \
                            cell_stage_bytes(nb, cell_zw(P), cell_cells(nb, cell_zw(P), cells)), s, nk, nb,          \
-                           cell_cells(nb, cell_zw(P), cells), Zr, rc, loc);                                       \
-    hipLaunchKernelGGL((k_condense_gather<P, NU>), GRID8(ne * NU * (P + 1) * nb, 256), 0, s, ne, nk, nb,          \
-                       facet_cell, facet_loc, loc, rhat)
+                           cell_cells(nb, cell_zw(P), cells), Zr, rc, loc)
     if (nu == 1) { switch (p) { case 1: CC(1, 1); break; case 2: CC(2, 1); break; case 3: CC(3, 1); break; } }
     else { switch (p) { case 1: CC(1, 2); break; case 2: CC(2, 2); break; case 3: CC(3, 2); break; } }
 #undef CC
+}
+void launch_condense_gather(int p, int nu, int nk, int ne, int nb, const double *loc, const int *facet_cell,
+                            const int *facet_loc, double *rhat, hipStream_t s) {
+#define CG(P, NU) hipLaunchKernelGGL((k_condense_gather<P, NU>), GRID8(ne * NU * (P + 1) * nb, 256), 0, s, ne, nk, nb, \
+                                     facet_cell, facet_loc, loc, rhat)
+    if (nu == 1) { switch (p) { case 1: CG(1, 1); break; case 2: CG(2, 1); break; case 3: CG(3, 1); break; } }
+    else { switch (p) { case 1: CG(1, 2); break; case 2: CG(2, 2); break; case 3: CG(3, 2); break; } }
+#undef CG
 }
 
 #define RL_REC(P, NU) (3 * (P + 1) * (P + 2) / 2 + 3 * (NU) * (P + 1))   // recovery row: A^-1 Mt and W entries
@@ -2334,8 +2389,11 @@ void launch_recover(int p, int nu, int nk, int nb, const double *Ar, const doubl
                     int cells) {
 #define RC(P, NU)                                                                                              \
     if (nb == 1)                                                                                               \
-        hipLaunchKernelGGL((k_recover_n1<P, NU>), GRID8(nk, RECOVER_TILE), 0, s, nk, Ar, Wr, cell_facet, cell_rev, \
-                           rc, lam, q);                                                                        \
+        hipLaunchKernelGGL((k_recover_s<P, NU, true>), cell_grid(nk, nb), dim3(RECOVER_TILE),                  \
+                           small_bytes(3 * (P + 1) * (P + 2) / 2, nb), s, nk, nb, Ar, Wr, cell_facet, cell_rev, rc, lam, q); \
+    else if (nb <= cell_small_dense(P))                                                                           \
+        hipLaunchKernelGGL((k_recover_s<P, NU, false>), cell_grid(nk, nb), dim3(RECOVER_TILE),                 \
+                           small_bytes(3 * (P + 1) * (P + 2) / 2, nb), s, nk, nb, Ar, Wr, cell_facet, cell_rev, rc, lam, q); \
     else                                                                                                       \
         hipLaunchKernelGGL((k_recover_b<P, NU>), GRID8((int64_t)nk * nb, cell_cells(nb, RL_REC(P, NU), cells) * nb), \
                            sizeof(double) * CELL_ROWS * RL_REC(P, NU) * cell_cells(nb, RL_REC(P, NU), cells), s, nk, \
