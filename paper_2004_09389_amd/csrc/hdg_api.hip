@@ -608,21 +608,38 @@ void dots(hdg_ctx *c, int nb, int nd, const double *X, int64_t xstride, const do
 
 // Reduction results the host needs are written by the kernels straight into
 // host-mapped memory (slots of 64 doubles in c->hlag, device view c->dlag):
-// no copy kernel is queued.  mark_lag() records when slot's values are final;
-// wait_lag() blocks until then.  The Krylov loops look at iteration j's
-// residual while iteration j+1 is already queued, so the GPU does not idle.
+// no copy kernel is queued.  All of them are norms or relative residuals, never
+// negative, so a slot is armed with -1 before its producer is queued and
+// wait_lag() watches the values arrive; that ends 10-20 us before an event or the
+// stream reports the producer's end.  The watch is bounded; then the stream decides.
+constexpr double LAG_PENDING = -1.0;
 double *lag_dev(hdg_ctx *c, int slot) { return c->dlag + 64 * slot; }
-void mark_lag(hdg_ctx *c, int slot, hipStream_t s) { HDG_HIP_CHECK(hipEventRecord(c->lag_ev[slot], s)); }
-const double *wait_lag(hdg_ctx *c, int slot) {
-    HDG_HIP_CHECK(hipEventSynchronize(c->lag_ev[slot]));
+void arm_lag(hdg_ctx *c, int slot, int nb) {
+    volatile double *h = c->hlag + 64 * slot;
+    for (int r = 0; r < nb; ++r) h[r] = LAG_PENDING;
+    __atomic_thread_fence(__ATOMIC_SEQ_CST);
+}
+const double *wait_lag(hdg_ctx *c, int slot, int nb, hipStream_t s) {
+    volatile double *h = c->hlag + 64 * slot;
+    const auto t0 = std::chrono::steady_clock::now();
+    for (int r = 0; r < nb;) {
+        if (h[r] != LAG_PENDING) {
+            ++r;
+        } else if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(2)) {
+            HDG_HIP_CHECK(hipStreamSynchronize(s));
+            for (; r < nb; ++r)
+                if (h[r] == LAG_PENDING) throw Error{HDG_EHIP, "a reduction wrote no result"};
+        }
+    }
+    __atomic_thread_fence(__ATOMIC_ACQUIRE);
     return c->hlag + 64 * slot;
 }
 
 // Blocking: dots of a single pair written to host slot 2.
 const double *dots_now(hdg_ctx *c, int nb, const double *x, const double *y, double *out, hipStream_t s) {
+    arm_lag(c, 2, nb);
     dots(c, nb, 1, x, 0, y, out, s, lag_dev(c, 2));
-    HDG_HIP_CHECK(hipStreamSynchronize(s));
-    return c->hlag + 64 * 2;
+    return wait_lag(c, 2, nb, s);
 }
 
 void fill_info(hdg_solve_info *info, int nb, int its, int refinements, const std::vector<double> &rel,
@@ -663,11 +680,11 @@ void true_residual(hdg_ctx *c, int nb, const double *rhat, const double *lam, do
             hdg::launch_trace_residual_f32(c->m, c->n_facet, nb, c->S64, c->nbr, lam, rhat,
                                            reinterpret_cast<float *>(out), s, c->rhs_block);
         check_launch();
+        arm_lag(c, 2, nb);
         hdg::launch_dots<float>(vec_len(c), nb, 1, reinterpret_cast<const float *>(out), 0,
                                 reinterpret_cast<const float *>(out), c->red, scal(c, SC_RR), lag_dev(c, 2), s);
         check_launch();
-        HDG_HIP_CHECK(hipStreamSynchronize(s));
-        h = c->hlag + 64 * 2;
+        h = wait_lag(c, 2, nb, s);
     } else {
         op_apply(c, nb, HDG_FP64, lam, rhat, out, s, HDG_KERNEL_RESIDUAL);
         h = dots_now(c, nb, out, out, scal(c, SC_RR), s);
@@ -711,6 +728,7 @@ int solve_pcg(hdg_ctx *c, int nb, const double *rhat, double *lam_user, hdg_solv
             // one iteration: w = S p, alpha = rz / (p.w), lam += alpha p, r -= alpha w, ||r||^2 -> slot,
             // z = V(r), rzn = r.z, p = z + (rzn / rz) p;  rz and rzn swap roles every iteration
             double *a = rzb[slot], *b = rzb[slot ^ 1];
+            arm_lag(c, slot, nb);
             run_step(c, graph_key(1, nb, HDG_FP64, slot), s, [&](hipStream_t st) {
                 op_apply(c, nb, HDG_FP64, c->kp, nullptr, c->kw, st, HDG_KERNEL_APPLY);
                 dots(c, nb, 1, c->kp, 0, c->kw, scal(c, SC_PW), st);
@@ -721,10 +739,9 @@ int solve_pcg(hdg_ctx *c, int nb, const double *rhat, double *lam_user, hdg_solv
                 hdg::launch_pcg_dir(n, nb, b, a, c->kz, c->kp, st);
                 check_launch();
             });
-            mark_lag(c, slot, s);
             ++its;
             if (pending >= 0) {
-                const double *h = wait_lag(c, pending);
+                const double *h = wait_lag(c, pending, nb, s);
                 bool done = true, bad = false;
                 for (int r = 0; r < nb; ++r) {
                     if (!std::isfinite(h[r])) bad = true;
@@ -742,10 +759,20 @@ int solve_pcg(hdg_ctx *c, int nb, const double *rhat, double *lam_user, hdg_solv
 // HDG_MIXED the Arnoldi process applies the FP32 operator and the
 // mixed-precision V-cycle, and a cycle ends once it has reduced its own
 // starting residual by inner_eta: the restarts are then FP64 iterative
-// refinement around a reduced-precision inner solve.  The residual estimate
-// of column j is examined while column j+1 is already queued.
+// refinement around a reduced-precision inner solve.
+//
+// The residual estimate of column j is examined while column j+1 is already queued, so
+// that the GPU does not idle, except where column j is likely to be the last: when
+// the estimates so far, carried on at their last rate, come within LAST_MARGIN of the
+// target, the host waits for column j before it queues another.  A column queued in vain
+// costs a whole iteration (2 ms of 31 per refinement on the level-7 sphere), a wait in
+// vain about 10 us.  The columns used, and so the result, are the same either way.
+//
+// zero: lam is zero on entry, so the first residual is rhat itself (its norm known) and the
+// first cycle's update need not read lam.
+constexpr double LAST_MARGIN = 10.0;
 int solve_fgmres(hdg_ctx *c, int nb, int vc_prec, int op_prec, double inner_eta, const double *rhat,
-                 double *lam, hdg_solve_info *info, hipStream_t s) {
+                 double *lam, hdg_solve_info *info, hipStream_t s, bool zero) {
     const int64_t n = vec_len(c);
     const int64_t vs = n * c->opt.max_rhs;   // basis slot, in doubles
     const int R = c->opt.restart;
@@ -778,20 +805,59 @@ int solve_fgmres(hdg_ctx *c, int nb, int vc_prec, int op_prec, double inner_eta,
     };
     while (true) {
         set32(false);
-        true_residual(c, nb, rhat, lam, c->kV, rel, s, f32);
+        const bool first = zero && cycles == 0;
+        if (first) {
+            for (int r = 0; r < nb; ++r) rel[r] = std::isfinite(c->hbn2[r]) ? (c->hbn2[r] > 0 ? 1.0 : 0.0) : c->hbn2[r];
+            if (f32) {   // rounded once into the FP32 basis, the norm that of the FP32 vector
+                float *v0 = reinterpret_cast<float *>(c->kV);
+                hdg::launch_round(n * nb, rhat, v0, s);
+                hdg::launch_dots<float>(n, nb, 1, v0, 0, v0, c->red, scal(c, SC_RR), nullptr, s);
+            } else {
+                hdg::launch_copy(n * nb, rhat, c->kV, s);
+            }
+            check_launch();
+        } else {
+            true_residual(c, nb, rhat, lam, c->kV, rel, s, f32);
+        }
         if (any_nonfinite(rel)) return done_info(HDG_EBREAKDOWN);
         if (all_below(rel, rtol)) return done_info(HDG_OK);
         if (its >= c->opt.maxit) return done_info(HDG_ENOTCONV);
         ++cycles;
         cyc0 = rel;
         set32(true);
-        hdg::launch_gmres_start(nb, R, scal(c, SC_RR), c->gm, scal(c, SC_BETA), s);
-        int k = 0, pending = -1;
-        auto converged = [&](const double *h) {
+        hdg::launch_gmres_start(nb, R, scal(c, first && !f32 ? SC_BN2 : SC_RR), c->gm, scal(c, SC_BETA), s);
+        int k = 0, seen = -1;   // seen: the last column whose estimate was examined
+        std::vector<double> last = cyc0, before;
+        auto target = [&](int r) { return std::max(rtol, inner_eta * cyc0[r]); };
+        // examine column i's estimate: true when the cycle ends with it
+        auto examine = [&](int i) {
+            const double *h = wait_lag(c, i & 1, nb, s);
+            seen = i;
+            before = last;
+            last.assign(h, h + nb);
+            bool all = true;
             for (int r = 0; r < nb; ++r) {
                 if (!std::isfinite(h[r])) return true;   // stop the cycle; the true residual reports it
-                if (!(h[r] <= std::max(rtol, inner_eta * cyc0[r]))) return false;
+                if (!(h[r] <= target(r))) all = false;
             }
+            if (all) return true;
+            // learned smoother judged by the mean residual reduction per iteration over this
+            // restart cycle; block-Jacobi takes over for the rest of the solve when it is too weak
+            if (c->use_mlp_now && i >= 1) {
+                for (int r = 0; r < nb; ++r)
+                    if (cyc0[r] > 0 && std::pow(h[r] / cyc0[r], 1.0 / (i + 1)) > c->opt.fallback_ratio) {
+                        c->use_mlp_now = false;
+                        ++fallbacks;
+                        break;
+                    }
+            }
+            return false;
+        };
+        // whether column seen + 1 is likely to end the cycle
+        auto near_end = [&] {
+            if (seen < 0) return false;
+            for (int r = 0; r < nb; ++r)
+                if (!(last[r] * std::min(1.0, last[r] / before[r]) <= LAST_MARGIN * target(r))) return false;
             return true;
         };
         for (int j = 0; j < R && its < c->opt.maxit; ++j) {
@@ -816,6 +882,7 @@ int solve_fgmres(hdg_ctx *c, int nb, int vc_prec, int op_prec, double inner_eta,
             const double *vscale = (j == 0) ? scal(c, SC_BETA) : scal(c, SC_HN);
             const bool one_pass = f32;
             c->gs_lag = (j == 0 || !one_pass) ? hdg::GsLag{} : hdg::GsLag{c->kV, vstride, j, c->hcol, c->gs_explicit};
+            arm_lag(c, slot, nb);
             run_step(c, graph_key(2 + (c->use_mlp_now ? 1 : 0), nb, vc_prec * 4 + op_prec, j), s, [&](hipStream_t st) {
                 vcycle(c, nb, vc_prec, Vj, Zj, st, vscale);
                 op_apply(c, nb, op_prec, Zj, nullptr, Vn, st, HDG_KERNEL_APPLY, c->vcyc32, c->kv32);
@@ -832,34 +899,18 @@ int solve_fgmres(hdg_ctx *c, int nb, int vc_prec, int op_prec, double inner_eta,
                 check_launch();
             });
             c->gs_lag = hdg::GsLag{};
-            mark_lag(c, slot, s);
             ++its;
             k = j + 1;
-            if (pending >= 0) {
-                const double *h = wait_lag(c, pending);
-                if (converged(h)) {
-                    k = j;   // column j was queued speculatively; the solution uses columns 0..j-1
-                    pending = -1;
-                    break;
-                }
-                // learned smoother judged by the mean residual reduction per iteration over
-                // this restart cycle (h holds the estimate after j iterations); block-Jacobi
-                // takes over for the rest of the solve when it is too weak
-                if (c->use_mlp_now && j >= 2) {
-                    for (int r = 0; r < nb; ++r)
-                        if (cyc0[r] > 0 && std::pow(h[r] / cyc0[r], 1.0 / j) > c->opt.fallback_ratio) {
-                            c->use_mlp_now = false;
-                            ++fallbacks;
-                            break;
-                        }
-                }
+            if (seen < j - 1 && examine(j - 1)) {
+                k = j;   // column j was queued speculatively; the solution uses columns 0..j-1
+                break;
             }
-            pending = slot;
+            if (near_end() && examine(j)) break;
         }
         hdg::launch_gmres_solve(nb, k, R, c->gm, c->hy, s);
         vt_call(c->vcyc32, [&](auto tag) {
             using VT = std::remove_pointer_t<decltype(tag)>;
-            hdg::launch_lincomb<VT>(n, nb, k, c->hy, vt<VT>(c->kZ), c->vcyc32 ? 2 * vs : vs, lam, s);
+            hdg::launch_lincomb<VT>(n, nb, k, c->hy, vt<VT>(c->kZ), c->vcyc32 ? 2 * vs : vs, first, lam, s);
         });
         check_launch();
     }
@@ -1320,7 +1371,6 @@ void setup_impl(const hdg_mesh *levels, int nlev, const int32_t *const *parents,
     HDG_HIP_CHECK(hipHostMalloc((void **)&c->hlag, sizeof(double) * 64 * 4,
                                 hipHostMallocMapped | hipHostMallocCoherent));
     HDG_HIP_CHECK(hipHostGetDevicePointer((void **)&c->dlag, c->hlag, 0));
-    for (int i = 0; i < 2; ++i) HDG_HIP_CHECK(hipEventCreateWithFlags(&c->lag_ev[i], hipEventDisableTiming));
     c->hbn2.assign(mr, 0.0);
     c->stage_rhat = dev_alloc<double>(c, vl);
 
@@ -1409,8 +1459,6 @@ void destroy_impl(hdg_ctx *c) {
     if (c->hscal) (void)hipHostFree(c->hscal);
     if (c->hlag) (void)hipHostFree(c->hlag);
     if (c->small_hinfo) (void)hipHostFree(c->small_hinfo);
-    for (int i = 0; i < 2; ++i)
-        if (c->lag_ev[i]) (void)hipEventDestroy(c->lag_ev[i]);
 }
 
 }  // namespace
@@ -1725,7 +1773,9 @@ extern "C" int hdg_mg_vcycle(hdg_ctx *c, int32_t nb, int32_t prec, const double 
 
 namespace {
 // Step 2 on the caller's stream (the argument checks are done by the callers)
-int solve_impl(hdg_ctx *c, int nb, const double *rhat, double *lam, hdg_solve_info *info, hipStream_t s) {
+// zero: lam holds zeros
+int solve_impl(hdg_ctx *c, int nb, const double *rhat, double *lam, hdg_solve_info *info, hipStream_t s,
+               bool zero = false) {
     c->use_mlp_now = c->opt.smoother == HDG_SMOOTH_MLP;
     const int kry = krylov_kind(c);
     HDG_REQUIRE(!(kry == HDG_KRYLOV_PCG && c->use_mlp_now), "the learned smoother is nonlinear: use FGMRES");
@@ -1738,10 +1788,16 @@ int solve_impl(hdg_ctx *c, int nb, const double *rhat, double *lam, hdg_solve_in
     for (int r = 0; r < nb; ++r) c->hbn2[r] = h[r];
     if (kry == HDG_KRYLOV_PCG) return solve_pcg(c, nb, rhat, lam, info, s);
     if (c->opt.precision == HDG_MIXED_IR)
-        return solve_fgmres(c, nb, HDG_MIXED, HDG_MIXED, c->opt.ir_inner_rtol, rhat, lam, info, s);
-    return solve_fgmres(c, nb, c->opt.precision, HDG_FP64, 0.0, rhat, lam, info, s);
+        return solve_fgmres(c, nb, HDG_MIXED, HDG_MIXED, c->opt.ir_inner_rtol, rhat, lam, info, s, zero);
+    return solve_fgmres(c, nb, c->opt.precision, HDG_FP64, 0.0, rhat, lam, info, s, zero);
 }
 }  // namespace
+
+int hdg::solve_from_zero(hdg_ctx *c, int nb, const double *rhat, double *lam, hdg_solve_info *info, hipStream_t s) {
+    const int status = solve_impl(c, nb, rhat, lam, info, s, true);
+    if (status == HDG_EBREAKDOWN) throw Error{HDG_EBREAKDOWN, "non-finite residual in the Krylov solve"};
+    return status;
+}
 
 extern "C" int hdg_solve(hdg_ctx *c, int32_t nb, const double *rhat, double *lam, hdg_solve_info *info,
                          void *stream) {
@@ -1777,7 +1833,7 @@ extern "C" int hdg_stage_solve(hdg_ctx *c, int32_t nb, const double *r_cell, dou
         condense(c, nb, r_cell, c->loc, c->stage_rhat, s, c->cell_cells);
         check_launch();
         HDG_HIP_CHECK(hipMemsetAsync(lam, 0, sizeof(double) * (size_t)vec_len(c) * nb, s));
-        status = solve_impl(c, nb, c->stage_rhat, lam, info, s);
+        status = solve_impl(c, nb, c->stage_rhat, lam, info, s, true);
         recover(c, nb, r_cell, lam, q_cell, s, c->cell_cells);
         check_launch();
         HDG_HIP_CHECK(hipStreamSynchronize(s));

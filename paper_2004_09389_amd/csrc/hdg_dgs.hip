@@ -490,7 +490,7 @@ void scale_cols(const Dgs &g, const std::vector<double> &c, const double *x, dou
 void lincomb(const Dgs &g, int nd, const std::vector<double> &coef, const double *Z, int64_t zstride, double *x) {
     HDG_HIP_CHECK(hipMemcpyAsync(g.c->dgs_coef, coef.data(), (size_t)nd * g.nb * sizeof(double),
                                  hipMemcpyHostToDevice, g.s));
-    launch_lincomb<double>(g.len, g.nb, nd, g.c->dgs_coef, Z, zstride, x, g.s);
+    launch_lincomb<double>(g.len, g.nb, nd, g.c->dgs_coef, Z, zstride, false, x, g.s);
     check_kernel_launch();
 }
 

@@ -542,8 +542,7 @@ extern "C" int hdg_imex_run(hdg_ctx *c, const hdg_imex_tableau *tab, double dt, 
                 }
                 hdg::check_abi(hdg_condense(c, nb, R[i], rhat, stream));
                 HDG_HIP_CHECK(hipMemsetAsync(lam, 0, (size_t)c->n_facet * c->m * nb * sizeof(double), st));
-                const int src = hdg_solve(c, nb, rhat, lam, si.data(), stream);
-                hdg::check_abi(src);
+                const int src = hdg::solve_from_zero(c, nb, rhat, lam, si.data(), st);
                 if (src == HDG_ENOTCONV) acc.status = HDG_ENOTCONV;
                 int it = 0;
                 for (int r = 0; r < nb; ++r) {

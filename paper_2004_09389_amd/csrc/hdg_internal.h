@@ -125,6 +125,8 @@ DenseMap make_dense(hdg_ctx *c, int n, const double *src);
 void *ctx_alloc(hdg_ctx *c, size_t bytes);
 // free one device allocation of the context
 void ctx_release(hdg_ctx *c, void *p, size_t bytes);
+// hdg_solve for lam holding zeros (device): HDG_OK or HDG_ENOTCONV, a breakdown thrown
+int solve_from_zero(hdg_ctx *c, int nb, const double *rhat, double *lam, hdg_solve_info *info, hipStream_t s);
 // each side's share of the DG trace of the cell field q at its facet nodes (hdg_imex.hip):
 // half [n_facet][2][facet_dofs][nrhs]; phi = hscale * field 0
 void launch_dg_half(const hdg_ctx *c, int nb, double hscale, const double *q, double *half, hipStream_t s);
@@ -223,7 +225,6 @@ struct hdg_ctx {
     std::vector<double> hbn2;                 // ||rhat||^2 per RHS (host)
     double *hlag = nullptr;                   // host-mapped landing slots for reduction results [4][64]
     double *dlag = nullptr;                   // device view of hlag
-    hipEvent_t lag_ev[2] = {nullptr, nullptr};
     int red_blocks = 0;
 
     // persistent single-launch solve of small systems (hdg_small.hip)

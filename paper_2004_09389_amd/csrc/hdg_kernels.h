@@ -247,9 +247,10 @@ void launch_pcg_update_norm(int64_t len, int nb, const double *num, const double
 void launch_pcg_dir(int64_t n, int nb, const double *num, const double *den, const double *z, double *p,
                     hipStream_t s);
 template <typename VT>
-void launch_lincomb(int64_t n, int nb, int nd, const double *y, const VT *Z, int64_t zstride, double *x,
+void launch_lincomb(int64_t n, int nb, int nd, const double *y, const VT *Z, int64_t zstride, bool zero, double *x,
                     hipStream_t s);
 void launch_copy(int64_t n, const double *src, double *dst, hipStream_t s);
+void launch_round(int64_t n, const double *src, float *dst, hipStream_t s);
 void launch_gmres_start(int nb, int restart, const double *beta2, double *gm, double *beta, hipStream_t s);
 void launch_gmres_solve(int nb, int k, int restart, const double *gm, double *y, hipStream_t s);
 void launch_sqrt(int nb, const double *in, double *out, hipStream_t s);

@@ -1350,18 +1350,23 @@ __global__ void k_pcg_dir(int64_t n, int nb, const double *__restrict__ num, con
     p[t] = z[t] + be * p[t];
 }
 
-// x += sum_{d < nd} y[d][r] Z_d
+// x += sum_{d < nd} y[d][r] Z_d; from zero (x = the sum) when set
 template <typename VT>
 __global__ void k_lincomb(int64_t n, int nb, int nd, const double *__restrict__ y, const VT *__restrict__ Z,
-                          int64_t zstride, double *__restrict__ x) {
+                          int64_t zstride, int zero, double *__restrict__ x) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n * nb) return;
     const int r = (int)(t % nb);
-    double s = x[t];
+    double s = zero ? 0.0 : x[t];
     for (int d = 0; d < nd; ++d) s += y[(size_t)d * nb + r] * (double)Z[(size_t)d * zstride + t];
     x[t] = s;
 }
 
+// dst = src rounded to FP32
+__global__ void k_round(int64_t n, const double *__restrict__ src, float *__restrict__ dst) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n) dst[t] = (float)src[t];
+}
 
 __global__ void k_copy(int64_t n, const double *__restrict__ src, double *__restrict__ dst) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -2446,9 +2451,9 @@ void launch_pcg_dir(int64_t n, int nb, const double *num, const double *den, con
     hipLaunchKernelGGL(k_pcg_dir, GRID(n * nb, 256), 0, s, n, nb, num, den, z, p);
 }
 template <typename VT>
-void launch_lincomb(int64_t n, int nb, int nd, const double *y, const VT *Z, int64_t zstride, double *x,
+void launch_lincomb(int64_t n, int nb, int nd, const double *y, const VT *Z, int64_t zstride, bool zero, double *x,
                     hipStream_t s) {
-    hipLaunchKernelGGL(k_lincomb<VT>, GRID(n * nb, 256), 0, s, n, nb, nd, y, Z, zstride, x);
+    hipLaunchKernelGGL(k_lincomb<VT>, GRID(n * nb, 256), 0, s, n, nb, nd, y, Z, zstride, zero ? 1 : 0, x);
 }
 template void launch_dots<double>(int64_t, int, int, const double *, int64_t, const double *, double *, double *,
                                   double *, hipStream_t);
@@ -2460,10 +2465,13 @@ template void launch_gs_norm_givens<double>(int64_t, int, int, const double *, c
 template void launch_gs_norm_givens<float>(int64_t, int, int, const double *, const float *, int64_t, float *,
                                            double *, double *, int, int, double *, const double *, double *,
                                            hipStream_t, const int *);
-template void launch_lincomb<double>(int64_t, int, int, const double *, const double *, int64_t, double *,
+template void launch_lincomb<double>(int64_t, int, int, const double *, const double *, int64_t, bool, double *,
                                      hipStream_t);
-template void launch_lincomb<float>(int64_t, int, int, const double *, const float *, int64_t, double *,
+template void launch_lincomb<float>(int64_t, int, int, const double *, const float *, int64_t, bool, double *,
                                     hipStream_t);
+void launch_round(int64_t n, const double *src, float *dst, hipStream_t s) {
+    hipLaunchKernelGGL(k_round, GRID(n, 256), 0, s, n, src, dst);
+}
 void launch_copy(int64_t n, const double *src, double *dst, hipStream_t s) {
     hipLaunchKernelGGL(k_copy, GRID(n, 256), 0, s, n, src, dst);
 }
