@@ -595,15 +595,20 @@ enum { SC_RR = 0, SC_RZ0, SC_RZ1, SC_PW, SC_BETA, SC_RES, SC_HN2, SC_HN, SC_BN2,
 
 double *scal(hdg_ctx *c, int slot) { return c->scal + (size_t)slot * c->opt.max_rhs; }
 int64_t vec_len(const hdg_ctx *c) { return (int64_t)c->n_facet * c->m; }
+// doubles from one basis vector to the next: whole 32-byte groups, so that every vector is aligned
+int64_t basis_slot(const hdg_ctx *c) { return (vec_len(c) * c->opt.max_rhs + 3) / 4 * 4; }
 
-// out (device, may be null) and host (host-mapped, may be null) receive the dots
-void dots(hdg_ctx *c, int nb, int nd, const double *X, int64_t xstride, const double *y, double *out,
-          hipStream_t s, double *host = nullptr) {
+// out (device, may be null) and host (host-mapped, may be null) receive the dots; defer: their
+// final sum may be left to the consumer
+hdg::PartialSums dots(hdg_ctx *c, int nb, int nd, const double *X, int64_t xstride, const double *y, double *out,
+                      hipStream_t s, double *host = nullptr, bool defer = false) {
+    hdg::PartialSums p;
     vt_call(c->kv32, [&](auto tag) {
         using VT = std::remove_pointer_t<decltype(tag)>;
-        hdg::launch_dots<VT>(vec_len(c), nb, nd, vt<VT>(X), xstride, vt<VT>(y), c->red, out, host, s);
+        p = hdg::launch_dots<VT>(vec_len(c), nb, nd, vt<VT>(X), xstride, vt<VT>(y), c->red, out, host, s, defer);
     });
     check_launch();
+    return p;
 }
 
 // Reduction results the host needs are written by the kernels straight into
@@ -731,12 +736,12 @@ int solve_pcg(hdg_ctx *c, int nb, const double *rhat, double *lam_user, hdg_solv
             arm_lag(c, slot, nb);
             run_step(c, graph_key(1, nb, HDG_FP64, slot), s, [&](hipStream_t st) {
                 op_apply(c, nb, HDG_FP64, c->kp, nullptr, c->kw, st, HDG_KERNEL_APPLY);
-                dots(c, nb, 1, c->kp, 0, c->kw, scal(c, SC_PW), st);
-                hdg::launch_pcg_update_norm(n, nb, a, scal(c, SC_PW), c->kp, c->kw, lam, c->kr, c->red,
+                const auto pw = dots(c, nb, 1, c->kp, 0, c->kw, scal(c, SC_PW), st, nullptr, true);
+                hdg::launch_pcg_update_norm(n, nb, a, scal(c, SC_PW), pw, c->kp, c->kw, lam, c->kr, c->red2,
                                             lag_dev(c, slot), st);
                 vcycle(c, nb, HDG_FP64, c->kr, c->kz, st);
-                dots(c, nb, 1, c->kr, 0, c->kz, b, st);
-                hdg::launch_pcg_dir(n, nb, b, a, c->kz, c->kp, st);
+                const auto rz = dots(c, nb, 1, c->kr, 0, c->kz, b, st, nullptr, true);
+                hdg::launch_pcg_dir(n, nb, b, a, rz, c->kz, c->kp, st);
                 check_launch();
             });
             ++its;
@@ -774,7 +779,7 @@ constexpr double LAST_MARGIN = 10.0;
 int solve_fgmres(hdg_ctx *c, int nb, int vc_prec, int op_prec, double inner_eta, const double *rhat,
                  double *lam, hdg_solve_info *info, hipStream_t s, bool zero) {
     const int64_t n = vec_len(c);
-    const int64_t vs = n * c->opt.max_rhs;   // basis slot, in doubles
+    const int64_t vs = basis_slot(c);        // basis slot, in doubles
     const int R = c->opt.restart;
     const double rtol = c->opt.rtol;
     // the inner solve of HDG_MIXED_IR (FP32 operator and V-cycle) keeps its basis and the
@@ -886,13 +891,13 @@ int solve_fgmres(hdg_ctx *c, int nb, int vc_prec, int op_prec, double inner_eta,
             run_step(c, graph_key(2 + (c->use_mlp_now ? 1 : 0), nb, vc_prec * 4 + op_prec, j), s, [&](hipStream_t st) {
                 vcycle(c, nb, vc_prec, Vj, Zj, st, vscale);
                 op_apply(c, nb, op_prec, Zj, nullptr, Vn, st, HDG_KERNEL_APPLY, c->vcyc32, c->kv32);
-                dots(c, nb, one_pass ? j + 2 : j + 1, c->kV, vstride, Vn, c->hcol, st);
+                const auto hp = dots(c, nb, one_pass ? j + 2 : j + 1, c->kV, vstride, Vn, c->hcol, st, nullptr, !one_pass);
                 if (one_pass)
                     hdg::launch_pyth_givens(nb, j, R, 1e-2, c->hcol, scal(c, SC_HN), c->gm, c->dbn, lag_dev(c, slot),
                                             c->gs_explicit, st);
                 vt_call(c->kv32, [&](auto tag) {
                     using VT = std::remove_pointer_t<decltype(tag)>;
-                    hdg::launch_gs_norm_givens<VT>(n, nb, j + 1, c->hcol, vt<VT>(c->kV), vstride, vt<VT>(Vn), c->red,
+                    hdg::launch_gs_norm_givens<VT>(n, nb, j + 1, c->hcol, hp, vt<VT>(c->kV), vstride, vt<VT>(Vn), c->red2,
                                                    scal(c, SC_HN), j, R, c->gm, c->dbn, lag_dev(c, slot), st,
                                                    one_pass ? c->gs_explicit : nullptr);
                 });
@@ -1333,11 +1338,12 @@ void setup_impl(const hdg_mesh *levels, int nlev, const int32_t *const *parents,
     const int Rr = opt.restart;
     const bool need_gmres = !(opt.krylov == HDG_KRYLOV_PCG);
     if (need_gmres) {
-        c->kV = dev_alloc<double>(c, vl * (Rr + 1));
-        c->kZ = dev_alloc<double>(c, vl * Rr);
+        c->kV = dev_alloc<double>(c, (size_t)basis_slot(c) * (Rr + 1));
+        c->kZ = dev_alloc<double>(c, (size_t)basis_slot(c) * Rr);
     }
     c->red_blocks = 2048;   // upper bound of red_grid() for any nrhs
     c->red = dev_alloc<double>(c, (size_t)c->red_blocks * (Rr + 1) * mr);
+    c->red2 = dev_alloc<double>(c, (size_t)c->red_blocks * mr);
     c->scal = dev_alloc<double>(c, (size_t)SC_COUNT * mr);
     c->hcol = dev_alloc<double>(c, (size_t)(Rr + 1) * mr);
     c->gs_explicit = dev_alloc<int>(c, 1);

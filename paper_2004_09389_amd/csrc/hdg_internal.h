@@ -212,7 +212,8 @@ struct hdg_ctx {
     // Krylov work
     double *kr = nullptr, *kz = nullptr, *kp = nullptr, *kw = nullptr, *klam = nullptr;
     double *kV = nullptr, *kZ = nullptr;      // FGMRES bases [(restart+1)][vec], [restart][vec]
-    double *red = nullptr;                    // reduction partials
+    double *red = nullptr;                    // reduction partials of the dot products
+    double *red2 = nullptr;                   // ... of the norms taken by the update kernels
     double *scal = nullptr;                   // device scalars [slot][max_rhs]
     double *hscal = nullptr;                  // pinned host mirror
     double *hcol = nullptr;                   // FGMRES Hessenberg column [restart+1][max_rhs]

@@ -226,9 +226,15 @@ void launch_recover(int p, int nu, int nk, int nb, const double *Ar, const doubl
                     int cells = 0);
 
 int red_grid(int64_t len, int nb);
+// Block sums of a dot-product launch left to their consumer (partial null: none left, out is final).
+struct PartialSums {
+    const double *partial = nullptr;
+    int nblk = 0;
+};
+// out[d][r] = X_d . y per right-hand side; defer: the final sum may be left to the consumer
 template <typename VT>
-void launch_dots(int64_t len, int nb, int nd, const VT *X, int64_t xstride, const VT *y, double *partial,
-                 double *out, double *host, hipStream_t s);
+PartialSums launch_dots(int64_t len, int nb, int nd, const VT *X, int64_t xstride, const VT *y, double *partial,
+                        double *out, double *host, hipStream_t s, bool defer = false);
 // ||w - sum_d h_d V_d|| of an orthonormal basis from the dot products alone
 // (hcol[j + 1] holds ||w||^2: the norm is sqrt(||w||^2 - sum_{d <= j} h_d^2)), then
 // the Givens step of FGMRES column j
@@ -237,14 +243,15 @@ void launch_dots(int64_t len, int nb, int nd, const VT *X, int64_t xstride, cons
 // kernel (GsLag); otherwise *expl = 1 and launch_gs_norm_givens with run = expl does it.
 void launch_pyth_givens(int nb, int j, int restart, double floor, const double *hcol, double *hn, double *gm,
                         const double *bnorm, double *resid_host, int *expl, hipStream_t s);
+// h: the dot products, or (dots given) where to keep them; partial: not the buffer dots lies in
 template <typename VT>
-void launch_gs_norm_givens(int64_t len, int nb, int nd, const double *h, const VT *V, int64_t vstride, VT *w,
+void launch_gs_norm_givens(int64_t len, int nb, int nd, double *h, PartialSums dots, const VT *V, int64_t vstride, VT *w,
                            double *partial, double *hn, int j, int restart, double *gm, const double *bnorm,
                            double *resid_host, hipStream_t s, const int *run = nullptr);
-void launch_pcg_update_norm(int64_t len, int nb, const double *num, const double *den, const double *p,
-                            const double *w, double *x, double *res, double *partial, double *rr_host,
+void launch_pcg_update_norm(int64_t len, int nb, const double *num, const double *den, PartialSums dots,
+                            const double *p, const double *w, double *x, double *res, double *partial, double *rr_host,
                             hipStream_t s);
-void launch_pcg_dir(int64_t n, int nb, const double *num, const double *den, const double *z, double *p,
+void launch_pcg_dir(int64_t n, int nb, double *num, const double *den, PartialSums dots, const double *z, double *p,
                     hipStream_t s);
 template <typename VT>
 void launch_lincomb(int64_t n, int nb, int nd, const double *y, const VT *Z, int64_t zstride, bool zero, double *x,

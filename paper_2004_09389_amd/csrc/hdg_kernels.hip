@@ -1186,43 +1186,76 @@ __global__ __launch_bounds__(256) void k_sum_final(int nblk, int nout, const dou
     }
 }
 
-__device__ void givens_column(int r, int nb, int j, int restart, const double *hcol, double hn, double *gm,
-                              const double *bnorm, double *resid) {
+// The block sums of a preceding dot-product launch, added by every block of their consumer
+// instead of by a launch of their own (k_sum_final, 3-4 us): worth it while the partials
+// are few (INLINE_BLOCKS, INLINE_OUT), as every block reads them all.  16 lanes per output.
+constexpr int INLINE_BLOCKS = 256, INLINE_OUT = 64;
+__device__ __forceinline__ void inline_sums(const PartialSums &p, int nout, double *sums, double *out) {
+    const int grp = threadIdx.x >> 4, l = threadIdx.x & 15;
+    for (int o = grp; o < nout; o += 16) {
+        double s = 0.0;
+        for (int b0 = l; b0 < p.nblk; b0 += 64) {
+            double v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int b = b0 + 16 * u;
+                v[u] = b < p.nblk ? p.partial[(size_t)b * nout + o] : 0.0;
+            }
+            s += (v[0] + v[1]) + (v[2] + v[3]);
+        }
+        s += __shfl_xor(s, 8, 16);
+        s += __shfl_xor(s, 4, 16);
+        s += __shfl_xor(s, 2, 16);
+        s += __shfl_xor(s, 1, 16);
+        if (l == 0) {
+            sums[o] = s;
+            if (out) out[o] = s;
+        }
+    }
+    __syncthreads();
+}
+
+// Givens step of FGMRES column j for right-hand side r: hc[0..j] the Hessenberg column, cs / sn the
+// earlier rotations (all preloaded), hn its last entry; col receives the rotated column.
+__device__ __forceinline__ void givens_step(int r, int j, int restart, const double *hc, const double *cs,
+                                            const double *sn, double hn, double *gm, const double *bnorm,
+                                            double *resid, double *col) {
     const int stride = (restart + 1) * restart + 2 * restart + (restart + 1);
     double *H = gm + (size_t)r * stride;
-    double *cs = H + (restart + 1) * restart;
-    double *sn = cs + restart;
-    double *g = sn + restart;
-    double col[65];
-    for (int i = 0; i <= j; ++i) col[i] = hcol[(size_t)i * nb + r];
-    col[j + 1] = hn;
+    double *gcs = H + (restart + 1) * restart, *gsn = gcs + restart, *g = gsn + restart;
+    const double gj = g[j], bn = bnorm[r];
+    double a = hc[0];
     for (int i = 0; i < j; ++i) {
-        const double a = col[i], b = col[i + 1];
+        const double b = hc[i + 1];
         col[i] = cs[i] * a + sn[i] * b;
-        col[i + 1] = -sn[i] * a + cs[i] * b;
+        a = -sn[i] * a + cs[i] * b;
     }
-    const double a = col[j], b = col[j + 1];
-    const double d = sqrt(a * a + b * b);
-    const double c = d > 0.0 ? a / d : 1.0, s = d > 0.0 ? b / d : 0.0;
-    cs[j] = c;
-    sn[j] = s;
+    const double d = sqrt(a * a + hn * hn);
+    const double c = d > 0.0 ? a / d : 1.0, s = d > 0.0 ? hn / d : 0.0;
     col[j] = d;
-    for (int i = 0; i <= j; ++i) H[(size_t)i * restart + j] = col[i];
-    const double gj = g[j];
+    const double gn = -s * gj;
+    resid[r] = bn > 0.0 ? fabs(gn) / bn : 0.0;
+    gcs[j] = c;
+    gsn[j] = s;
     g[j] = c * gj;
-    g[j + 1] = -s * gj;
-    const double bn = bnorm[r];
-    resid[r] = bn > 0.0 ? fabs(g[j + 1]) / bn : 0.0;
+    g[j + 1] = gn;
 }
 
 // w -= sum_d h[d] V_d (classical Gram-Schmidt) and block partials of ||w||^2
 template <typename VT>
 __global__ __launch_bounds__(256) void k_gs_update_norm(int64_t len, int nb, int nd, const double *__restrict__ h,
+                                                        PartialSums dots, double *__restrict__ hout,
                                                         const VT *__restrict__ V, int64_t vstride,
                                                         VT *__restrict__ w, double *__restrict__ partial,
                                                         const int *__restrict__ run) {
     if (run && !*run) return;   // the lagged step was taken instead (k_pyth_givens)
     __shared__ double sh[1][256];
+    __shared__ double hs[INLINE_OUT];
+    const double *hh = h;
+    if (dots.partial) {   // the coefficients from the dot products' block sums; one block keeps them
+        inline_sums(dots, nd * nb, hs, blockIdx.x == 0 ? hout : nullptr);
+        hh = hs;
+    }
     const int rpb = rows_per_block(nb);
     const int tid = threadIdx.x;
     const int rl = tid / nb, r = tid - rl * nb;
@@ -1242,7 +1275,7 @@ __global__ __launch_bounds__(256) void k_gs_update_norm(int64_t len, int nb, int
                 s[u] = (double)w[tt[u]];
             }
             for (int d = 0; d < nd; ++d) {
-                const double hd = h[(size_t)d * nb + r];
+                const double hd = hh[d * nb + r];
 #pragma unroll
                 for (int u = 0; u < GS_ROWS; ++u) s[u] -= hd * (double)V[(size_t)d * vstride + tt[u]];
             }
@@ -1268,13 +1301,25 @@ __global__ __launch_bounds__(256) void k_norm_givens(int nblk, int nb, const dou
                                                      const double *__restrict__ bnorm, double *__restrict__ resid,
                                                      const int *__restrict__ run) {
     if (run && !*run) return;
-    const int r = blockIdx.x;
-    const double v = block_sum_partials(partial, nblk, nb, r);
-    if (threadIdx.x == 0) {
+    __shared__ double hc[65], cs[64], sn[64], col[65];
+    const int r = blockIdx.x, tid = threadIdx.x;
+    const int stride = (restart + 1) * restart + 2 * restart + (restart + 1);
+    double *H = gm + (size_t)r * stride;
+    if (tid <= j) {
+        hc[tid] = hcol[(size_t)tid * nb + r];
+        if (tid < j) {
+            cs[tid] = H[(restart + 1) * restart + tid];
+            sn[tid] = H[(restart + 1) * restart + restart + tid];
+        }
+    }
+    const double v = block_sum_partials(partial, nblk, nb, r);   // (its barriers order the loads above)
+    if (tid == 0) {
         const double n = sqrt(fmax(v, 0.0));
         hn[r] = n;
-        givens_column(r, nb, j, restart, hcol, n, gm, bnorm, resid);
+        givens_step(r, j, restart, hc, cs, sn, n, gm, bnorm, resid, col);
     }
+    __syncthreads();
+    if (tid <= j) H[(size_t)tid * restart + j] = col[tid];
 }
 
 // The norm of w - sum_{d <= j} h_d V_d from the dot products of the same pass
@@ -1308,12 +1353,18 @@ __global__ __launch_bounds__(64) void k_pyth_givens(int nb, int j, int restart, 
     if (bad || r >= nb) return;
     const double n = sqrt(s);
     hn[r] = n;
-    givens_column(r, nb, j, restart, hcol, n, gm, bnorm, resid);
+    const int stride = (restart + 1) * restart + 2 * restart + (restart + 1);
+    double *H = gm + (size_t)r * stride;
+    const double *cs = H + (restart + 1) * restart;
+    double hc[65], col[65];
+    for (int i = 0; i <= j; ++i) hc[i] = hcol[(size_t)i * nb + r];
+    givens_step(r, j, restart, hc, cs, cs + restart, n, gm, bnorm, resid, col);
+    for (int i = 0; i <= j; ++i) H[(size_t)i * restart + j] = col[i];
 }
 
 // PCG update x += alpha p, r -= alpha w (alpha = num/den) and partials of ||r||^2
 __global__ __launch_bounds__(256) void k_pcg_update_norm(int64_t len, int nb, const double *__restrict__ num,
-                                                         const double *__restrict__ den,
+                                                         const double *__restrict__ den, PartialSums dots,
                                                          const double *__restrict__ p, const double *__restrict__ w,
                                                          double *__restrict__ x, double *__restrict__ res,
                                                          double *__restrict__ partial) {
@@ -1321,9 +1372,11 @@ __global__ __launch_bounds__(256) void k_pcg_update_norm(int64_t len, int nb, co
     const int rpb = rows_per_block(nb);
     const int tid = threadIdx.x;
     const int rl = tid / nb, r = tid - rl * nb;
+    __shared__ double ds[INLINE_OUT];
+    if (dots.partial) inline_sums(dots, nb, ds, nullptr);   // p.w from its block sums
     double acc = 0.0;
     if (rl < rpb) {
-        const double d = den[r];
+        const double d = dots.partial ? ds[r] : den[r];
         const double al = d != 0.0 ? num[r] / d : 0.0;
         for (int64_t i = (int64_t)blockIdx.x * rpb + rl; i < len; i += (int64_t)gridDim.x * rpb) {
             const size_t t = (size_t)i * nb + r;
@@ -1339,14 +1392,18 @@ __global__ __launch_bounds__(256) void k_pcg_update_norm(int64_t len, int nb, co
 }
 
 
-// p = z + beta p, beta[r] = num[r] / den[r]
-__global__ void k_pcg_dir(int64_t n, int nb, const double *__restrict__ num, const double *__restrict__ den,
-                          const double *__restrict__ z, double *__restrict__ p) {
+// p = z + beta p, beta[r] = num[r] / den[r]; num from the block sums of its dot products when given
+// (then written by one block)
+__global__ __launch_bounds__(256) void k_pcg_dir(int64_t n, int nb, double *__restrict__ num,
+                                                 const double *__restrict__ den, PartialSums dots,
+                                                 const double *__restrict__ z, double *__restrict__ p) {
+    __shared__ double ns[INLINE_OUT];
+    if (dots.partial) inline_sums(dots, nb, ns, blockIdx.x == 0 ? num : nullptr);
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n * nb) return;
     const int r = (int)(t % nb);
     const double d = den[r];
-    const double be = d != 0.0 ? num[r] / d : 0.0;
+    const double be = d != 0.0 ? (dots.partial ? ns[r] : num[r]) / d : 0.0;
     p[t] = z[t] + be * p[t];
 }
 
@@ -1386,21 +1443,24 @@ __global__ void k_gmres_start(int nb, int restart, const double *__restrict__ be
     beta[r] = b;
 }
 
-// y = H(0:k,0:k)^-1 g(0:k) by back substitution, written as y[i][r]
-__global__ void k_gmres_solve(int nb, int k, int restart, const double *__restrict__ gm, double *__restrict__ y) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nb) return;
+// y = H(0:k,0:k)^-1 g(0:k) by back substitution, written as y[i][r]: one wavefront per right-hand side,
+// lane i on row i (k <= 64), the triangle staged in LDS so that its loads are in flight together
+__global__ __launch_bounds__(64) void k_gmres_solve(int nb, int k, int restart, const double *__restrict__ gm,
+                                                    double *__restrict__ y) {
+    __shared__ double h[64 * 65];
+    const int r = blockIdx.x, i = threadIdx.x;
     const int stride = (restart + 1) * restart + 2 * restart + (restart + 1);
     const double *H = gm + (size_t)r * stride;
-    const double *g = H + (restart + 1) * restart + 2 * restart;
-    double yy[64];
-    for (int i = k - 1; i >= 0; --i) {
-        double s = g[i];
-        for (int l = i + 1; l < k; ++l) s -= H[(size_t)i * restart + l] * yy[l];
-        const double d = H[(size_t)i * restart + i];
-        yy[i] = d != 0.0 ? s / d : 0.0;
+    for (int t = i; t < k * k; t += 64) h[(t / k) * 65 + t % k] = H[(size_t)(t / k) * restart + t % k];
+    double s = i < k ? H[(restart + 1) * restart + 2 * restart + i] : 0.0, yi = 0.0;
+    __syncthreads();
+    for (int l = k - 1; l >= 0; --l) {
+        const double d = h[l * 65 + l];
+        const double yl = d != 0.0 ? __shfl(s, l, 64) / d : 0.0;
+        if (i < l) s -= h[i * 65 + l] * yl;
+        if (i == l) yi = yl;
     }
-    for (int i = 0; i < k; ++i) y[(size_t)i * nb + r] = yy[i];
+    if (i < k) y[(size_t)i * nb + r] = yi;
 }
 
 __global__ void k_sqrt(int nb, const double *__restrict__ in, double *__restrict__ out) {
@@ -1712,6 +1772,191 @@ __global__ void k_p1_restrict4(int nc, int nb, const int *__restrict__ crow, con
             for (int q = 0; q < 4; ++q) s[q] = g + u < cnt ? s[q] + t[u][q] : s[q];
     }
     p1_st4(bc + (size_t)c * nb + r0, s);
+}
+
+// ---------------------------------------------------------------- Krylov reductions, four values per thread
+//
+// The dot products and the Gram-Schmidt update stream whole basis vectors and are bound by
+// loads in flight: a thread takes four consecutive entries (16 or 32 bytes a vector)
+// instead of one.  GW = 4: four right-hand sides of a row, nb = 4 NQ with NQ a power of
+// two up to 16; GW = 1: one right-hand side, four rows.  A thread keeps its group of
+// right-hand sides over its grid-strided rows; sums are combined by a butterfly in each
+// wavefront, then over the four wavefronts in order.  Other batch sizes, and vectors that
+// are not 16-byte aligned, take the scalar kernels.
+// Level-7 sphere, 32 right-hand sides (FP32 basis, 252 MB a vector): dot products
+// 251 -> 172 us per launch (6 columns on average, 1.13 GB: 4.5 -> 6.6 TB/s), the solution update
+// 543 -> 442 us; 56x56 torus, p = 2, one: dot products 7.6 -> 5.6 us.
+
+template <int GW, typename VT>
+__device__ __forceinline__ void load_group(const VT *__restrict__ p, int64_t i, int64_t n, VT (&v)[4]) {
+    if (GW == 4 || i + 4 <= n) {
+        load_raw<4>(p + i, v);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = i + q < n ? p[i + q] : VT(0);
+    }
+}
+
+// part[wave][k][rhs] -> sums over the wavefronts; acc: GW per k
+template <int GW, int KC>
+__device__ __forceinline__ void group_sums(double (&acc)[KC][GW], int kc, int nb, int nq, double (*part)[KC][64]) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+#pragma unroll
+    for (int k = 0; k < KC; ++k)
+        if (k < kc) {
+#pragma unroll
+            for (int g = 0; g < GW; ++g) {
+                double v = acc[k][g];
+                for (int off = nq; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
+                if (lane < nq) part[wv][k][lane * GW + g] = v;
+            }
+        }
+    __syncthreads();
+}
+
+template <int GW, typename VT>
+__global__ __launch_bounds__(256) void k_mdot4(int64_t n, int nb, int nd, const VT *__restrict__ X, int64_t xstride,
+                                               const VT *__restrict__ y, double *__restrict__ partial) {
+    constexpr int KC = RED_CHUNK, U = 2;
+    __shared__ double part[4][KC][64];
+    const int tid = threadIdx.x, nq = GW == 4 ? nb / 4 : 1;
+    const int64_t step = (int64_t)gridDim.x * 1024, first = ((int64_t)blockIdx.x * 256 + tid) * 4;
+    for (int d0 = 0; d0 < nd; d0 += KC) {
+        const int kc = min(KC, nd - d0);
+        const VT *Xd = X + (size_t)d0 * xstride;
+        double acc[KC][GW];
+#pragma unroll
+        for (int k = 0; k < KC; ++k)
+#pragma unroll
+            for (int g = 0; g < GW; ++g) acc[k][g] = 0.0;
+        for (int64_t i = first; i < n; i += U * step) {
+            VT yv[U][4];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (i + u * step < n) {
+                    load_group<GW>(y, i + u * step, n, yv[u]);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) yv[u][q] = VT(0);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < KC; ++k)
+                if (k < kc) {
+                    VT xv[U][4];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) load_group<GW>(Xd + (size_t)k * xstride, i + u * step < n ? i + u * step : i, n, xv[u]);
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) acc[k][GW == 4 ? q : 0] += (double)xv[u][q] * (double)yv[u][q];
+                }
+        }
+        group_sums<GW, KC>(acc, kc, nb, nq, part);
+        for (int o = tid; o < kc * nb; o += 256) {
+            const int k = o / nb, r = o - k * nb;
+            partial[((size_t)blockIdx.x * nd + d0 + k) * nb + r] =
+                ((part[0][k][r] + part[1][k][r]) + part[2][k][r]) + part[3][k][r];
+        }
+        __syncthreads();
+    }
+}
+
+// w -= sum_d h[d] V_d and block partials of ||w||^2 (h: global, or summed here, see k_gs_update_norm)
+template <int GW, typename VT>
+__global__ __launch_bounds__(256) void k_gs_update_norm4(int64_t n, int nb, int nd, const double *__restrict__ h,
+                                                         PartialSums dots, double *__restrict__ hout,
+                                                         const VT *__restrict__ V, int64_t vstride,
+                                                         VT *__restrict__ w, double *__restrict__ partial,
+                                                         const int *__restrict__ run) {
+    if (run && !*run) return;   // the lagged step was taken instead (k_pyth_givens)
+    __shared__ double part[4][1][64];
+    __shared__ double hs[INLINE_OUT];
+    const int tid = threadIdx.x, nq = GW == 4 ? nb / 4 : 1;
+    const double *hh = h;
+    if (dots.partial) {
+        inline_sums(dots, nd * nb, hs, blockIdx.x == 0 ? hout : nullptr);
+        hh = hs;
+    }
+    const int64_t step = (int64_t)gridDim.x * 1024, first = ((int64_t)blockIdx.x * 256 + tid) * 4;
+    const int r0 = GW == 4 ? 4 * (tid & (nq - 1)) : 0;
+    double acc[1][GW];
+#pragma unroll
+    for (int g = 0; g < GW; ++g) acc[0][g] = 0.0;
+    for (int64_t i = first; i < n; i += step) {
+        VT wv[4];
+        load_group<GW>(w, i, n, wv);
+        double s[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s[q] = (double)wv[q];
+        int d = 0;
+        for (; d + 2 <= nd; d += 2) {
+            VT a[4], b[4];
+            load_group<GW>(V + (size_t)d * vstride, i, n, a);
+            load_group<GW>(V + (size_t)(d + 1) * vstride, i, n, b);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                s[q] -= hh[d * nb + r0 + (GW == 4 ? q : 0)] * (double)a[q];
+                s[q] -= hh[(d + 1) * nb + r0 + (GW == 4 ? q : 0)] * (double)b[q];
+            }
+        }
+        if (d < nd) {
+            VT a[4];
+            load_group<GW>(V + (size_t)d * vstride, i, n, a);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) s[q] -= hh[d * nb + r0 + (GW == 4 ? q : 0)] * (double)a[q];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            wv[q] = (VT)s[q];   // the norm is that of the vector as stored
+            acc[0][GW == 4 ? q : 0] += (double)wv[q] * (double)wv[q];
+        }
+        if (GW == 4 || i + 4 <= n) {
+            store_raw<4>(w + i, wv);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (i + q < n) w[i + q] = wv[q];
+        }
+    }
+    group_sums<GW, 1>(acc, 1, nb, nq, part);
+    if (tid < nb) partial[(size_t)blockIdx.x * nb + tid] = ((part[0][0][tid] + part[1][0][tid]) + part[2][0][tid]) + part[3][0][tid];
+}
+
+// x += sum_d y[d][r] Z_d, four entries per thread (nb % 4 == 0 or nb = 1)
+template <typename VT>
+__global__ __launch_bounds__(256) void k_lincomb4(int64_t n, int nb, int nd, const double *__restrict__ y,
+                                                  const VT *__restrict__ Z, int64_t zstride, int zero,
+                                                  double *__restrict__ x) {
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (i >= n) return;
+    const int r0 = nb == 1 ? 0 : (int)(i % nb), ri = nb == 1 ? 0 : 1;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    if (!zero) load_group<1>(x, i, n, s);
+    int d = 0;
+    for (; d + 2 <= nd; d += 2) {
+        VT a[4], b[4];
+        load_group<1>(Z + (size_t)d * zstride, i, n, a);
+        load_group<1>(Z + (size_t)(d + 1) * zstride, i, n, b);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            s[q] += y[(size_t)d * nb + r0 + ri * q] * (double)a[q];
+            s[q] += y[(size_t)(d + 1) * nb + r0 + ri * q] * (double)b[q];
+        }
+    }
+    if (d < nd) {
+        VT a[4];
+        load_group<1>(Z + (size_t)d * zstride, i, n, a);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s[q] += y[(size_t)d * nb + r0 + ri * q] * (double)a[q];
+    }
+    if (i + 4 <= n) {
+        store_raw<4>(x + i, s);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (i + q < n) x[i + q] = s[q];
+    }
 }
 
 // ---------------------------------------------------------------- dense level products
@@ -2417,19 +2662,45 @@ int red_grid(int64_t len, int nb) {
     return (int)blocks;
 }
 
+// four values per thread: 0 no, 1 one right-hand side, 4 groups of four (see k_mdot4)
+static int red_group(int nb, const void *a, const void *b, int64_t stride_bytes) {
+    if ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b) | (uintptr_t)stride_bytes) % 16 != 0) return 0;
+    if (nb == 1) return 1;
+    const int nq = nb / 4;
+    return nb % 4 == 0 && nq <= 16 && (nq & (nq - 1)) == 0 ? 4 : 0;
+}
+static int red_grid4(int64_t n) { return (int)std::min<int64_t>(2048, std::max<int64_t>(1, (n + 2047) / 2048)); }
+
 template <typename VT>
-void launch_dots(int64_t len, int nb, int nd, const VT *X, int64_t xstride, const VT *y, double *partial,
-                 double *out, double *host, hipStream_t s) {
-    const int g = red_grid(len, nb);
-    hipLaunchKernelGGL(k_mdot_partial<VT>, dim3(g), dim3(256), 0, s, len, nb, nd, X, xstride, y, partial);
+PartialSums launch_dots(int64_t len, int nb, int nd, const VT *X, int64_t xstride, const VT *y, double *partial,
+                        double *out, double *host, hipStream_t s, bool defer) {
+    const int grp = red_group(nb, X, y, xstride * (int64_t)sizeof(VT));
+    const int g = grp ? red_grid4(len * nb) : red_grid(len, nb);
+    if (grp == 4)
+        hipLaunchKernelGGL((k_mdot4<4, VT>), dim3(g), dim3(256), 0, s, len * nb, nb, nd, X, xstride, y, partial);
+    else if (grp == 1)
+        hipLaunchKernelGGL((k_mdot4<1, VT>), dim3(g), dim3(256), 0, s, len, nb, nd, X, xstride, y, partial);
+    else
+        hipLaunchKernelGGL(k_mdot_partial<VT>, dim3(g), dim3(256), 0, s, len, nb, nd, X, xstride, y, partial);
+    if (defer && g <= INLINE_BLOCKS && nd * nb <= INLINE_OUT) return PartialSums{partial, g};
     hipLaunchKernelGGL(k_sum_final, dim3(nd * nb), dim3(256), 0, s, g, nd * nb, partial, out, host);
+    return PartialSums{};
 }
 template <typename VT>
-void launch_gs_norm_givens(int64_t len, int nb, int nd, const double *h, const VT *V, int64_t vstride, VT *w,
+void launch_gs_norm_givens(int64_t len, int nb, int nd, double *h, PartialSums dots, const VT *V, int64_t vstride, VT *w,
                            double *partial, double *hn, int j, int restart, double *gm, const double *bnorm,
                            double *resid_host, hipStream_t s, const int *run) {
-    const int g = red_grid(len, nb);
-    hipLaunchKernelGGL(k_gs_update_norm<VT>, dim3(g), dim3(256), 0, s, len, nb, nd, h, V, vstride, w, partial, run);
+    const int grp = red_group(nb, V, w, vstride * (int64_t)sizeof(VT));
+    const int g = grp ? red_grid4(len * nb) : red_grid(len, nb);
+    if (grp == 4)
+        hipLaunchKernelGGL((k_gs_update_norm4<4, VT>), dim3(g), dim3(256), 0, s, len * nb, nb, nd, h, dots, h, V, vstride,
+                           w, partial, run);
+    else if (grp == 1)
+        hipLaunchKernelGGL((k_gs_update_norm4<1, VT>), dim3(g), dim3(256), 0, s, len, nb, nd, h, dots, h, V, vstride, w,
+                           partial, run);
+    else
+        hipLaunchKernelGGL(k_gs_update_norm<VT>, dim3(g), dim3(256), 0, s, len, nb, nd, h, dots, h, V, vstride, w, partial,
+                           run);
     hipLaunchKernelGGL(k_norm_givens, dim3(nb), dim3(256), 0, s, g, nb, partial, hn, j, restart, h, gm, bnorm,
                        resid_host, run);
 }
@@ -2438,33 +2709,37 @@ void launch_pyth_givens(int nb, int j, int restart, double floor, const double *
     hipLaunchKernelGGL(k_pyth_givens, dim3(1), dim3(64), 0, s, nb, j, restart, floor, hcol, hn, gm, bnorm, resid_host,
                        expl);
 }
-void launch_pcg_update_norm(int64_t len, int nb, const double *num, const double *den, const double *p,
-                            const double *w, double *x, double *res, double *partial, double *rr_host,
+void launch_pcg_update_norm(int64_t len, int nb, const double *num, const double *den, PartialSums dots,
+                            const double *p, const double *w, double *x, double *res, double *partial, double *rr_host,
                             hipStream_t s) {
     const int g = red_grid(len, nb);
-    hipLaunchKernelGGL(k_pcg_update_norm, dim3(g), dim3(256), 0, s, len, nb, num, den, p, w, x, res, partial);
+    hipLaunchKernelGGL(k_pcg_update_norm, dim3(g), dim3(256), 0, s, len, nb, num, den, dots, p, w, x, res, partial);
     hipLaunchKernelGGL(k_sum_final, dim3(nb), dim3(256), 0, s, g, nb, partial, (double *)nullptr, rr_host);
 }
 
-void launch_pcg_dir(int64_t n, int nb, const double *num, const double *den, const double *z, double *p,
+void launch_pcg_dir(int64_t n, int nb, double *num, const double *den, PartialSums dots, const double *z, double *p,
                     hipStream_t s) {
-    hipLaunchKernelGGL(k_pcg_dir, GRID(n * nb, 256), 0, s, n, nb, num, den, z, p);
+    hipLaunchKernelGGL(k_pcg_dir, GRID(n * nb, 256), 0, s, n, nb, num, den, dots, z, p);
 }
 template <typename VT>
 void launch_lincomb(int64_t n, int nb, int nd, const double *y, const VT *Z, int64_t zstride, bool zero, double *x,
                     hipStream_t s) {
+    if ((nb == 1 || nb % 4 == 0) && (reinterpret_cast<uintptr_t>(Z) | reinterpret_cast<uintptr_t>(x) |
+                                     (uintptr_t)(zstride * (int64_t)sizeof(VT))) % 16 == 0) {
+        hipLaunchKernelGGL(k_lincomb4<VT>, GRID((n * nb + 3) / 4, 256), 0, s, n * nb, nb, nd, y, Z, zstride, zero ? 1 : 0, x);
+        return;
+    }
     hipLaunchKernelGGL(k_lincomb<VT>, GRID(n * nb, 256), 0, s, n, nb, nd, y, Z, zstride, zero ? 1 : 0, x);
 }
-template void launch_dots<double>(int64_t, int, int, const double *, int64_t, const double *, double *, double *,
-                                  double *, hipStream_t);
-template void launch_dots<float>(int64_t, int, int, const float *, int64_t, const float *, double *, double *,
-                                 double *, hipStream_t);
-template void launch_gs_norm_givens<double>(int64_t, int, int, const double *, const double *, int64_t, double *,
-                                            double *, double *, int, int, double *, const double *, double *,
+#define INST_KRY(VT)                                                                                               \
+    template PartialSums launch_dots<VT>(int64_t, int, int, const VT *, int64_t, const VT *, double *, double *,   \
+                                         double *, hipStream_t, bool);                                             \
+    template void launch_gs_norm_givens<VT>(int64_t, int, int, double *, PartialSums, const VT *, int64_t, VT *,   \
+                                            double *, double *, int, int, double *, const double *, double *,      \
                                             hipStream_t, const int *);
-template void launch_gs_norm_givens<float>(int64_t, int, int, const double *, const float *, int64_t, float *,
-                                           double *, double *, int, int, double *, const double *, double *,
-                                           hipStream_t, const int *);
+INST_KRY(double)
+INST_KRY(float)
+#undef INST_KRY
 template void launch_lincomb<double>(int64_t, int, int, const double *, const double *, int64_t, bool, double *,
                                      hipStream_t);
 template void launch_lincomb<float>(int64_t, int, int, const double *, const float *, int64_t, bool, double *,
@@ -2479,7 +2754,7 @@ void launch_gmres_start(int nb, int restart, const double *beta2, double *gm, do
     hipLaunchKernelGGL(k_gmres_start, GRID(nb, 64), 0, s, nb, restart, beta2, gm, beta);
 }
 void launch_gmres_solve(int nb, int k, int restart, const double *gm, double *y, hipStream_t s) {
-    hipLaunchKernelGGL(k_gmres_solve, GRID(nb, 64), 0, s, nb, k, restart, gm, y);
+    hipLaunchKernelGGL(k_gmres_solve, dim3(nb), dim3(64), 0, s, nb, k, restart, gm, y);
 }
 void launch_sqrt(int nb, const double *in, double *out, hipStream_t s) {
     hipLaunchKernelGGL(k_sqrt, GRID(nb, 64), 0, s, nb, in, out);
