@@ -445,9 +445,11 @@ typedef struct {
                                      smoothing kernel: 1 or 2 (default 1), or 4 = four consecutive
                                      right-hand sides of one facet with 16-byte loads (applies when
                                      nrhs is a multiple of 4, else 1 is used) */
-    int32_t rhs_block;          /* facet-row kernels (apply, residual, sweep) at nrhs = 4, 8, ..., 64:
-                                   1 = one thread per (facet, rhs); 4 = four right-hand sides per
-                                   thread with the block's rows staged in LDS (default 4) */
+    int32_t rhs_block;          /* facet-row kernels (apply, residual, sweep) and P1 level kernels:
+                                   1 = one thread per (facet or vertex, rhs); 4 = where the batch and
+                                   the mesh are large enough, the block's facet rows are staged in
+                                   LDS and P1 threads take four right-hand sides (default 4); the
+                                   results are the same bit for bit */
     int32_t cell_cells;         /* cells per block of the batched condensation and recovery
                                    kernels (nrhs >= 2; a block is cells x nrhs threads): 0 = the
                                    most that fit in 256 threads and 64 KiB of staged rows (default),

@@ -2134,7 +2134,7 @@ extern "C" int hdg_autotune(hdg_ctx *c, int32_t nb, hdg_tuning *chosen, void *st
             }
         }
         c->mlp_spl = best_spl;
-        // facet-row kernels: one thread per (facet, rhs) or RHS-blocked with LDS-staged rows
+        // facet-row kernels: one thread per (facet, rhs) or LDS-staged rows
         HDG_HIP_CHECK(hipMemsetAsync(c->vx2, 0, bytes, s));
         best = 1e300;
         int best_rb = 1;

@@ -184,8 +184,8 @@ void launch_restrict_trace(int p, int nv, int nb, const int *vf_row, const int *
 
 // P1 level kernels; f32: the level vectors (b, x, y, xc, r, bc) hold float values
 // in their double buffers (the V-cycle of a mixed-precision solve)
-// P1 level launchers: rb == 4 with nb % 4 == 0 takes four right-hand sides per
-// thread (the same bits as rb == 1).
+// P1 level launchers: rb == 4 takes four right-hand sides per thread where nb % 4 == 0
+// and the level is large enough (the same bits as rb == 1).
 void launch_p1_first(int n, int nb, const double *dinv, double omega, const double *b, double *x, hipStream_t s,
                      bool f32 = false, int rb = 1);
 void launch_p1_pre2(int n, int W, int nb, const int *col, const double *val, const double *diag,

@@ -1473,16 +1473,25 @@ __global__ void k_sqrt(int nb, const double *__restrict__ in, double *__restrict
 #define GRID(n, b) dim3((unsigned)(((n) + (b) - 1) / (b))), dim3(b)
 // grid padded to a multiple of N_XCD blocks, for kernels indexed through xcd_block()
 
-// ------------------------------------------------------------------ RHS-blocked facet-row kernels
+// ------------------------------------------------------------------ facet-row kernels with staged rows
 //
-// With many right-hand sides the per-(facet, rhs) kernels above re-read the
-// facet's matrix row once per right-hand side.  These variants give each
-// thread RB = 4 consecutive right-hand sides of one facet (two 16-byte loads
-// per facet node) and stage the rows of the block's 64 facets in LDS with
-// coalesced 16-byte loads, so every row leaves L2 once per block.
-// Block = 64 facets x (nb / RB) threads; nb / RB must be a power of two <= 16.
-constexpr int RB_FACETS = 64;
-
+// With several right-hand sides the per-(facet, rhs) kernels above re-read the
+// facet's matrix row once per right-hand side.  These variants stage the rows
+// of the block's F facets in LDS with coalesced 16-byte loads, so every row
+// leaves L2 once per block, and give each thread RB consecutive right-hand
+// sides of one facet.  Block = F facets x (nb / RB) threads.
+//
+// What bounds them is memory, through the latency of four neighbour fetches in
+// turn: few registers (eight waves per SIMD) hide it better than more values
+// per thread or all fetches at once.  A thread takes 16 bytes of each vector
+// (RB = 2 FP64 or 4 FP32 values) where the batch divides, so that neighbouring
+// lanes read neighbouring bytes.  FP64 operator, 491520 facets, p = 3, 32
+// right-hand sides: RB = 4 310 us (4.3 TB/s, every other 16 bytes of a line left
+// to the lane's next load, 106 registers), RB = 2 277 us (4.8 TB/s, the rate of a
+// large copy); the FP32 sweep there: RB = 2 212 us, RB = 4 175 us (6 TB/s).
+// 122880 facets, p = 3, 4 right-hand sides: RB = 4 48, RB = 2 25, one thread per
+// (facet, rhs) 30 us.  All five facets' values in registers at once (101-128
+// registers): 1.3 times slower at 32 right-hand sides, p = 2.
 template <typename MT>
 __device__ __forceinline__ float lds_entry_f(const MT *p) { return (float)*p; }
 template <>
@@ -1495,18 +1504,18 @@ __device__ __forceinline__ typename Acc<MT>::type lds_entry(const MT *p) {
     else return lds_entry_f<MT>(p);
 }
 
-// stage the G 16-byte groups of the rows of facets f0 .. f0 + 63 as [g][64][V]
-template <typename MT, int G>
+// stage the G 16-byte groups of the rows of facets f0 .. f0 + F - 1 as [g][F][V]
+template <typename MT, int G, int F>
 __device__ __forceinline__ void stage_rows(MT *sm, const MT *__restrict__ S, int f0, int ne) {
     // four 16-byte loads per lane go out before their LDS stores
-    constexpr int V = Wide<MT>::V, W = G * RB_FACETS, U = 4;
+    constexpr int V = Wide<MT>::V, W = G * F, U = 4;
     const size_t NE = (size_t)ne;
     const int step = blockDim.x;
     for (int i0 = threadIdx.x; i0 < W; i0 += U * step) {
         u32x4_t v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int i = i0 + u * step, g = i / RB_FACETS, e = f0 + (i - g * RB_FACETS);
+            const int i = i0 + u * step, g = i / F, e = f0 + (i - g * F);
             v[u] = u32x4_t{0u, 0u, 0u, 0u};
             if (i < W && e < ne) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(S + ((size_t)g * NE + e) * V));
         }
@@ -1518,9 +1527,20 @@ __device__ __forceinline__ void stage_rows(MT *sm, const MT *__restrict__ S, int
     }
 }
 
+// One or two values are read and written as one vector that is aligned as a
+// single value is; more in 16-byte pieces.
+template <int RB, typename T>
+struct RhsPair {
+    static constexpr bool use = RB < 16 / (int)sizeof(T) || RB == 2;
+    typedef T type __attribute__((ext_vector_type(RB), aligned(sizeof(T))));
+};
 template <int RB, typename T>
 __device__ __forceinline__ void load_rb(const T *__restrict__ p, double (&d)[RB]) {
-    if constexpr (std::is_same<T, double>::value) {
+    if constexpr (RhsPair<RB, T>::use) {
+        const typename RhsPair<RB, T>::type a = *reinterpret_cast<const typename RhsPair<RB, T>::type *>(p);
+#pragma unroll
+        for (int q = 0; q < RB; ++q) d[q] = a[q];
+    } else if constexpr (std::is_same<T, double>::value) {
 #pragma unroll
         for (int q = 0; q < RB; q += 2) {
             const dbl2_t a = *reinterpret_cast<const dbl2_t *>(p + q);
@@ -1541,7 +1561,12 @@ __device__ __forceinline__ void load_rb(const T *__restrict__ p, double (&d)[RB]
 template <int RB, typename T>
 __device__ __forceinline__ void store_rb(T *__restrict__ p, const double (&d)[RB]) {
     // streaming stores: the outputs are not read again by this launch
-    if constexpr (std::is_same<T, double>::value) {
+    if constexpr (RhsPair<RB, T>::use) {
+        typename RhsPair<RB, T>::type a;
+#pragma unroll
+        for (int q = 0; q < RB; ++q) a[q] = (T)d[q];
+        __builtin_nontemporal_store(a, reinterpret_cast<typename RhsPair<RB, T>::type *>(p));
+    } else if constexpr (std::is_same<T, double>::value) {
 #pragma unroll
         for (int q = 0; q < RB; q += 2)
             __builtin_nontemporal_store(dbl2_t{d[q], d[q + 1]}, reinterpret_cast<dbl2_t *>(p + q));
@@ -1556,7 +1581,11 @@ __device__ __forceinline__ void store_rb(T *__restrict__ p, const double (&d)[RB
 // RB consecutive values in their stored type, 16 bytes per load
 template <int RB, typename T>
 __device__ __forceinline__ void load_raw(const T *__restrict__ p, T (&d)[RB]) {
-    if constexpr (std::is_same<T, double>::value) {
+    if constexpr (RhsPair<RB, T>::use) {
+        const typename RhsPair<RB, T>::type a = *reinterpret_cast<const typename RhsPair<RB, T>::type *>(p);
+#pragma unroll
+        for (int q = 0; q < RB; ++q) d[q] = a[q];
+    } else if constexpr (std::is_same<T, double>::value) {
 #pragma unroll
         for (int q = 0; q < RB; q += 2) {
             const dbl2_t a = *reinterpret_cast<const dbl2_t *>(p + q);
@@ -1599,6 +1628,11 @@ template <int RB, typename T, typename C>
 __device__ __forceinline__ void store_ct(T *__restrict__ p, const C (&d)[RB]) {
     if constexpr (std::is_same<C, double>::value) {
         store_rb<RB>(p, d);
+    } else if constexpr (RhsPair<RB, T>::use) {
+        typename RhsPair<RB, T>::type a;
+#pragma unroll
+        for (int q = 0; q < RB; ++q) a[q] = d[q];
+        __builtin_nontemporal_store(a, reinterpret_cast<typename RhsPair<RB, T>::type *>(p));
     } else {
 #pragma unroll
         for (int q = 0; q < RB; q += 4)
@@ -2113,14 +2147,14 @@ __global__ void k_unit_cols(int n, int col0, int ncol, double *__restrict__ b) {
 // Latency: a lane requests its four neighbour ids and its own facet's values
 // before the block stages its rows, so those waits overlap the staging; each
 // neighbour then costs one wait (its values), not two (id, then values).
-template <int M, typename MT, typename XT, typename YT, int RB, typename BT = YT>
+template <int M, typename MT, typename XT, typename YT, int RB, int F, typename BT>
 __global__ __launch_bounds__(1024) void k_trace_apply_rb(int ne, int nb, const MT *__restrict__ S,
                                                          const int *__restrict__ nbr, const XT *__restrict__ x,
                                                          const BT *__restrict__ b, YT *__restrict__ y) {
     using AT = typename Acc<MT>::type;
     constexpr int V = Wide<MT>::V, C = 5 * M * M, G = padded(C, V) / V;
-    __shared__ __attribute__((aligned(16))) MT sm[G * RB_FACETS * V];
-    const int f0 = xcd_block() * RB_FACETS;
+    __shared__ __attribute__((aligned(16))) MT sm[G * F * V];
+    const int f0 = xcd_block() * F;
     const int tpf = nb / RB;
     const int el = threadIdx.x / tpf, r0 = (threadIdx.x - el * tpf) * RB, e = f0 + el;
     const bool live = e < ne;
@@ -2136,7 +2170,7 @@ __global__ __launch_bounds__(1024) void k_trace_apply_rb(int ne, int nb, const M
         for (int j = 0; j < 4; ++j) id[j] = nbr[(size_t)j * NE + e];
         fetch(e, xa);
     }
-    stage_rows<MT, G>(sm, S, f0, ne);
+    stage_rows<MT, G, F>(sm, S, f0, ne);
     __syncthreads();
     if (!live) return;
     AT acc[M][RB];
@@ -2150,7 +2184,7 @@ __global__ __launch_bounds__(1024) void k_trace_apply_rb(int ne, int nb, const M
 #pragma unroll
             for (int k = 0; k < M; ++k) {
                 const int c = (j * M + a) * M + k;
-                const AT w = lds_entry<MT>(sm + ((size_t)(c / V) * RB_FACETS + el) * V + c % V);
+                const AT w = lds_entry<MT>(sm + ((size_t)(c / V) * F + el) * V + c % V);
 #pragma unroll
                 for (int q = 0; q < RB; ++q) acc[a][q] += w * (AT)xv[k][q];
             }
@@ -2180,11 +2214,8 @@ __global__ __launch_bounds__(1024) void k_trace_apply_rb(int ne, int nb, const M
 }
 
 // the generalised sweep y = a0 x' + a1 z0 - a3 sum_j T_j x'_j + a2 xprev' (SweepCoef)
-// The FP32 sweep with bf16 rows is held to 80 registers (six waves per SIMD).
-template <typename MT, typename VT>
-constexpr int sweep_rb_waves() { return std::is_same<MT, __hip_bfloat16>::value && std::is_same<VT, float>::value ? 6 : 1; }
-template <int M, typename MT, typename VT, int RB>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(sweep_rb_waves<MT, VT>(), 8))) void k_sweep_rb(int ne, int nb, const MT *__restrict__ T,
+template <int M, typename MT, typename VT, int RB, int F>
+__global__ __launch_bounds__(1024) void k_sweep_rb(int ne, int nb, const MT *__restrict__ T,
                                                    const int *__restrict__ nbr, const VT *__restrict__ x,
                                                    const VT *__restrict__ z0, const VT *__restrict__ qc,
                                                    const int *__restrict__ fvert, SweepCoef cf,
@@ -2193,8 +2224,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(sweep_rb_w
     using CT = SweepT<VT>;
     constexpr int P = M - 1;
     constexpr int V = Wide<MT>::V, C = 4 * M * M, G = padded(C, V) / V;
-    __shared__ __attribute__((aligned(16))) MT sm[G * RB_FACETS * V];
-    const int f0 = xcd_block() * RB_FACETS;
+    __shared__ __attribute__((aligned(16))) MT sm[G * F * V];
+    const int f0 = xcd_block() * F;
     const int tpf = nb / RB;
     const int el = threadIdx.x / tpf, r0 = (threadIdx.x - el * tpf) * RB, e = f0 + el;
     const bool live = e < ne;
@@ -2215,7 +2246,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(sweep_rb_w
                 iv[j][1] = fvert[2 * id[j] + 1];
             }
     }
-    stage_rows<MT, G>(sm, T, f0, ne);
+    stage_rows<MT, G, F>(sm, T, f0, ne);
     __syncthreads();
     if (!live) return;
     AT acc[M][RB];
@@ -2251,7 +2282,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(sweep_rb_w
 #pragma unroll
             for (int k = 0; k < M; ++k) {
                 const int c = (j * M + a) * M + k;
-                const AT w = lds_entry<MT>(sm + ((size_t)(c / V) * RB_FACETS + el) * V + c % V);
+                const AT w = lds_entry<MT>(sm + ((size_t)(c / V) * F + el) * V + c % V);
 #pragma unroll
                 for (int q = 0; q < RB; ++q) acc[a][q] += w * xv[k][q];
             }
@@ -2358,15 +2389,6 @@ __global__ __launch_bounds__(256) void k_jacobi0_rb(int ne, int nb, const MT *__
     }
 }
 
-// RHS-blocked launch applies when nb / 4 is a power of two <= 16
-bool rhs_blocked(int nb, int rhs_block) {
-    if (rhs_block != 4 || nb < 4 || nb % 4 != 0) return false;
-    const int t = nb / 4;
-    return t <= 16 && (t & (t - 1)) == 0;
-}
-
-#define GRID_RB(ne, nb) dim3((unsigned)((((ne) + RB_FACETS - 1) / RB_FACETS + N_XCD - 1) / N_XCD * N_XCD)), dim3(RB_FACETS * ((nb) / 4))
-
 #define GRID8(n, b) dim3((unsigned)((((n) + (b) - 1) / (b) + N_XCD - 1) / N_XCD * N_XCD)), dim3(b)
 
 void launch_cell_condense(int p, int nu, int nk, const double *corners, const double *ref, CellParams cp,
@@ -2390,9 +2412,45 @@ void launch_facet_rows(int p, int nu, int ne, int nk, const double *Sloc, const 
 }
 
 // Facet-row launchers take M, the trace unknowns per facet: p + 1 (upwind) or
-// 2 (p + 1) (Lax-Friedrichs).  The RHS-blocked forms stage 64 facets' rows in
-// LDS and are built for M <= 4.
-bool rhs_blocked_m(int M, int nb, int rhs_block) { return M <= 4 && rhs_blocked(nb, rhs_block); }
+// 2 (p + 1) (Lax-Friedrichs).  The forms with LDS-staged rows are built for M <= 4.
+constexpr int64_t SIMD_LANES = 256 * 4 * 64;   // lanes of one wavefront on every SIMD of the chip
+struct RowShape {
+    int rb = 0, f = 0;   // right-hand sides per thread (0: one thread per (facet, rhs)), facets per block
+    int threads = 0;
+    unsigned grid = 0;
+};
+static RowShape row_shape(int ne, int nb, int rb) {
+    RowShape h;
+    h.f = nb / rb <= 16 ? 64 : 32;
+    if (nb / rb * h.f > 1024) return h;
+    h.rb = rb;
+    h.threads = nb / rb * h.f;
+    h.grid = (unsigned)(((ne + h.f - 1) / h.f + N_XCD - 1) / N_XCD * N_XCD);
+    return h;
+}
+// The rows are staged where the batch is large enough; vb: bytes of a vector entry.
+// Operator on FP64 vectors: from three right-hand sides on (122880 facets, p = 2,
+// staged against per-(facet, rhs): 3: 15.0 / 16.4 us, 5: 19.3 / 23.7, 16: 31.3 / 54.3;
+// 2: 15.8 / 12.1).  An FP64 sweep reads fewer row bytes per right-hand side (four
+// blocks) and gains later (V-cycle with sweeps staged against not, p = 3, 4 right-hand
+// sides: 232 / 201 us; p = 2, 8: 191 / 220).  Where one thread per (facet, rhs) is under
+// two wavefronts per SIMD the launch is one latency chain and the staging barrier only
+// adds to it (V-cycle at 12288 facets, 8 right-hand sides 51.0 / 49.5, 16: 53.3 / 58.7).
+// FP32 vectors halve what a lane fetches: from nine on (whole FP32 solve with
+// refinement, 122880 facets: p = 2, 8 right-hand sides 2297 / 2275 us, 10: 2863 / 2986,
+// 16: 3090 / 3304; p = 3, 8: 3324 / 3248, 16: 4306 / 4675).
+static int rows_per_thread(int nb, int vb) { return vb == 4 && nb % 4 == 0 ? 4 : nb % 2 == 0 ? 2 : 1; }
+static RowShape apply_shape(int M, int ne, int nb, int rhs_block, int vb) {
+    if (M > 4 || nb < (vb == 4 ? 9 : 3) || rhs_block == 1) return RowShape{};
+    return row_shape(ne, nb, rows_per_thread(nb, vb));
+}
+static RowShape sweep_shape(int M, int ne, int nb, int rhs_block, int vb) {
+    if (M > 4 || nb < (vb == 4 ? 9 : 8) || nb % 2 != 0 || rhs_block == 1 || (int64_t)ne * nb < 2 * SIMD_LANES)
+        return RowShape{};
+    return row_shape(ne, nb, rows_per_thread(nb, vb));
+}
+#define ROWS_LAUNCH(h, K, R, FF, ...) \
+    if ((h).rb == R && (h).f == FF) hipLaunchKernelGGL((K), dim3((h).grid), dim3((h).threads), 0, s, __VA_ARGS__)
 
 #define M_SWITCH(X) \
     switch (M) { case 2: X(2); break; case 3: X(3); break; case 4: X(4); break; case 6: X(6); break; case 8: X(8); break; }
@@ -2401,8 +2459,13 @@ bool rhs_blocked_m(int M, int nb, int rhs_block) { return M <= 4 && rhs_blocked(
 template <typename MT, typename XT, typename YT>
 void launch_trace_apply(int M, int ne, int nb, const MT *S, const int *nbr, const XT *x, const YT *b, YT *y,
                         hipStream_t s, int rhs_block) {
-    if (rhs_blocked_m(M, nb, rhs_block)) {
-#define TAB(MM) hipLaunchKernelGGL((k_trace_apply_rb<MM, MT, XT, YT, 4>), GRID_RB(ne, nb), 0, s, ne, nb, S, nbr, x, b, y)
+    if (const RowShape h = apply_shape(M, ne, nb, rhs_block, sizeof(*x)); h.rb) {
+#define TAB(MM) \
+    ROWS_LAUNCH(h, (k_trace_apply_rb<MM, MT, XT, YT, 1, 64, YT>), 1, 64, ne, nb, S, nbr, x, b, y); \
+    ROWS_LAUNCH(h, (k_trace_apply_rb<MM, MT, XT, YT, 1, 32, YT>), 1, 32, ne, nb, S, nbr, x, b, y); \
+    ROWS_LAUNCH(h, (k_trace_apply_rb<MM, MT, XT, YT, 2, 64, YT>), 2, 64, ne, nb, S, nbr, x, b, y); \
+    ROWS_LAUNCH(h, (k_trace_apply_rb<MM, MT, XT, YT, 2, 32, YT>), 2, 32, ne, nb, S, nbr, x, b, y); \
+    if constexpr (sizeof(XT) == 4) ROWS_LAUNCH(h, (k_trace_apply_rb<MM, MT, XT, YT, 4, 64, YT>), 4, 64, ne, nb, S, nbr, x, b, y)
         M_SWITCH_RB(TAB)
 #undef TAB
         return;
@@ -2417,8 +2480,12 @@ void launch_trace_apply(int M, int ne, int nb, const MT *S, const int *nbr, cons
 // FP32 inner solve of a refinement step)
 void launch_trace_residual_f32(int M, int ne, int nb, const double *S, const int *nbr, const double *x,
                                const double *b, float *y, hipStream_t s, int rhs_block) {
-    if (rhs_blocked_m(M, nb, rhs_block)) {
-#define TAB(MM) hipLaunchKernelGGL((k_trace_apply_rb<MM, double, double, float, 4, double>), GRID_RB(ne, nb), 0, s, ne, nb, S, nbr, x, b, y)
+    if (const RowShape h = apply_shape(M, ne, nb, rhs_block, sizeof(*x)); h.rb) {
+#define TAB(MM) \
+    ROWS_LAUNCH(h, (k_trace_apply_rb<MM, double, double, float, 1, 64, double>), 1, 64, ne, nb, S, nbr, x, b, y); \
+    ROWS_LAUNCH(h, (k_trace_apply_rb<MM, double, double, float, 1, 32, double>), 1, 32, ne, nb, S, nbr, x, b, y); \
+    ROWS_LAUNCH(h, (k_trace_apply_rb<MM, double, double, float, 2, 64, double>), 2, 64, ne, nb, S, nbr, x, b, y); \
+    ROWS_LAUNCH(h, (k_trace_apply_rb<MM, double, double, float, 2, 32, double>), 2, 32, ne, nb, S, nbr, x, b, y)
         M_SWITCH_RB(TAB)
 #undef TAB
         return;
@@ -2471,8 +2538,11 @@ template <typename MT, typename VT>
 void launch_sweep(int M, int ne, int nb, const MT *T, const int *nbr, const VT *x, const VT *z0, const double *qc,
                   const int *fvert, SweepCoef cf, VT *y, hipStream_t s, int rhs_block) {
     const VT *qv = reinterpret_cast<const VT *>(qc);   // P1 values in the sweep's vector type
-    if (rhs_blocked_m(M, nb, rhs_block)) {
-#define SWB(MM) hipLaunchKernelGGL((k_sweep_rb<MM, MT, VT, 4>), GRID_RB(ne, nb), 0, s, ne, nb, T, nbr, x, z0, qv, fvert, cf, y)
+    if (const RowShape h = sweep_shape(M, ne, nb, rhs_block, sizeof(VT)); h.rb) {
+#define SWB(MM) \
+    ROWS_LAUNCH(h, (k_sweep_rb<MM, MT, VT, 2, 64>), 2, 64, ne, nb, T, nbr, x, z0, qv, fvert, cf, y); \
+    ROWS_LAUNCH(h, (k_sweep_rb<MM, MT, VT, 2, 32>), 2, 32, ne, nb, T, nbr, x, z0, qv, fvert, cf, y); \
+    if constexpr (sizeof(VT) == 4) ROWS_LAUNCH(h, (k_sweep_rb<MM, MT, VT, 4, 64>), 4, 64, ne, nb, T, nbr, x, z0, qv, fvert, cf, y)
         M_SWITCH_RB(SWB)
 #undef SWB
         return;
@@ -2509,13 +2579,17 @@ static const VT *pv(const double *p) { return reinterpret_cast<const VT *>(p); }
 #define P1_TYPED(CALL) \
     if (f32) { using VT = float; CALL; } else { using VT = double; CALL; }
 
-// rb == 4 with nb % 4 == 0: four right-hand sides per thread (same bits)
-static bool p1_r4(int rb, int nb) { return rb == 4 && nb % 4 == 0; }
+// Four right-hand sides per thread pay where the launch keeps a wavefront per SIMD
+// all the same; below, the longer thread is the launch's latency.  Four per thread
+// from n nb >= 0 / 131072 / 524288 on, whole solve: finest level of 40962 vertices,
+// p = 2, 4 right-hand sides 2600 / 2426 / 2395 us, 8 (FP32 with refinement): 2314 /
+// 2257 / 2275, 10242 vertices, p = 1, 16: 1307 / 1266 / 1290.
+static bool p1_r4(int rb, int nb, int n) { return rb == 4 && nb % 4 == 0 && (int64_t)n * nb >= 4 * SIMD_LANES; }
 #define P1_GRID(n, nb, r4) GRID8((int64_t)(n) * ((r4) ? (nb) / 4 : (nb)), 256)
 
 void launch_p1_first(int n, int nb, const double *dinv, double omega, const double *b, double *x, hipStream_t s,
                      bool f32, int rb) {
-    const bool r4 = p1_r4(rb, nb);
+    const bool r4 = p1_r4(rb, nb, n);
     P1_TYPED(if (r4) hipLaunchKernelGGL(k_p1_first4<VT>, P1_GRID(n, nb, r4), 0, s, n, nb, dinv, omega, pv<VT>(b),
                                         pv<VT>(x));
              else hipLaunchKernelGGL(k_p1_first<VT>, P1_GRID(n, nb, r4), 0, s, n, nb, dinv, omega, pv<VT>(b),
@@ -2523,7 +2597,7 @@ void launch_p1_first(int n, int nb, const double *dinv, double omega, const doub
 }
 void launch_p1_pre2(int n, int W, int nb, const int *col, const double *val, const double *diag,
                     const double *dinv, double omega, const double *b, double *x, hipStream_t s, bool f32, int rb) {
-    const bool r4 = p1_r4(rb, nb);
+    const bool r4 = p1_r4(rb, nb, n);
 #define PRE2(K, WW) hipLaunchKernelGGL((K<WW, VT>), P1_GRID(n, nb, r4), 0, s, n, W, nb, col, val, diag, dinv, omega, \
                                        pv<VT>(b), pv<VT>(x))
     P1_TYPED(if (r4) { if (W == 6) PRE2(k_p1_pre2_4, 6); else PRE2(k_p1_pre2_4, 0); }
@@ -2535,7 +2609,7 @@ void launch_p1_pre2(int n, int W, int nb, const int *col, const double *val, con
 void launch_p1_sweep(int n, int W, int nb, const int *col, const double *val, const double *diag,
                      const double *dinv, double omega, const double *b, double *x, const double *xc,
                      const int *parents, double *y, hipStream_t s, bool f32, int rb) {
-    const bool r4 = p1_r4(rb, nb);
+    const bool r4 = p1_r4(rb, nb, n);
 #define SWP(K, WW) hipLaunchKernelGGL((K<WW, VT>), P1_GRID(n, nb, r4), 0, s, n, W, nb, col, val, diag, dinv, omega, \
                                       pv<VT>(b), pv<VT>(x), pv<VT>(y))
     P1_TYPED(
@@ -2554,7 +2628,7 @@ void launch_p1_sweep(int n, int W, int nb, const int *col, const double *val, co
 #undef SWPP
 void launch_p1_resid(int n, int W, int nb, const int *col, const double *val, const double *diag,
                      const double *b, const double *x, double *y, hipStream_t s, bool f32, int rb) {
-    const bool r4 = p1_r4(rb, nb);
+    const bool r4 = p1_r4(rb, nb, n);
 #define RES(K, WW) hipLaunchKernelGGL((K<WW, VT>), P1_GRID(n, nb, r4), 0, s, n, W, nb, col, val, diag, pv<VT>(b), \
                                       pv<VT>(x), pv<VT>(y))
     P1_TYPED(if (r4) { if (W == 6) RES(k_p1_resid4, 6); else RES(k_p1_resid4, 0); }
@@ -2563,7 +2637,7 @@ void launch_p1_resid(int n, int W, int nb, const int *col, const double *val, co
 }
 void launch_p1_restrict(int nc, int nb, const int *crow, const int *ccol, const double *cw, const double *r,
                         double *bc, hipStream_t s, bool f32, int rb) {
-    const bool r4 = p1_r4(rb, nb);
+    const bool r4 = p1_r4(rb, nb, nc);
     P1_TYPED(if (r4) hipLaunchKernelGGL(k_p1_restrict4<VT>, P1_GRID(nc, nb, r4), 0, s, nc, nb, crow, ccol, cw,
                                         pv<VT>(r), pv<VT>(bc));
              else hipLaunchKernelGGL(k_p1_restrict<VT>, P1_GRID(nc, nb, r4), 0, s, nc, nb, crow, ccol, cw, pv<VT>(r),
