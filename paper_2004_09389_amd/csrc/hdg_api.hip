@@ -1393,7 +1393,10 @@ void setup_impl(const hdg_mesh *levels, int nlev, const int32_t *const *parents,
         const size_t with_ops = hdg::small_lds_bytes(ne, m, lv.data(), (int)lv.size(), true, nB);
         const size_t lds =
             with_ops <= limit ? with_ops : hdg::small_lds_bytes(ne, m, lv.data(), (int)lv.size(), false, nB);
-        if (lds <= limit && hdg::small_prepare(c->p, lds) == hipSuccess) {
+        // the row-wise form keeps Gram-Schmidt partials in three trace vectors
+        const bool room = with_ops <= limit ||
+                          3 * (size_t)ne * m >= (size_t)(hdg::SMALL_MAXR + 1) * hdg::SMALL_ROW_THREADS / 64;
+        if (lds <= limit && room && hdg::small_prepare(c->p, lds) == hipSuccess) {
             c->small_ok = true;
             c->small_stage_ops = with_ops <= limit;
             c->small_lds = lds;

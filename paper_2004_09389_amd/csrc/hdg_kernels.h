@@ -263,7 +263,8 @@ void launch_gmres_solve(int nb, int k, int restart, const double *gm, double *y,
 void launch_sqrt(int nb, const double *in, double *out, hipStream_t s);
 
 // persistent single-workgroup solve of small trace systems (hdg_small.hip)
-constexpr int SMALL_THREADS = 256;    // threads per workgroup (one workgroup per right-hand side)
+constexpr int SMALL_THREADS = 256;    // threads per workgroup (one workgroup per right-hand side), operators in LDS
+constexpr int SMALL_ROW_THREADS = 512;   // the same, operators in global memory: one row of a facet per thread
 constexpr int SMALL_MAXR = 32;        // largest FGMRES restart length of the persistent solve
 constexpr int SMALL_P1_DENSE = 64;    // finest P1 levels up to this size apply the V-cycle as its matrix
 // The operators the persistent solve copies into LDS, packed once at setup into

@@ -10,8 +10,9 @@
 // omega D^-1 S_j and omega D^-1, the neighbour and vertex tables, the P1 level
 // matrices and the dense coarsest inverse (otherwise they are read from global
 // memory, where they stay cached after the first iteration).  A workgroup of
-// 256 threads owns the facets (vertices, cells) thread-cyclically, and every
-// phase whose output is read at other items ends with a workgroup barrier.
+// 256 or 512 threads owns the facets or their rows (vertices, cells) thread-
+// cyclically, and every phase whose output is read at other items ends with a
+// workgroup barrier.
 //
 // The arithmetic is the multi-launch path's: PCG (symmetric case) or flexible
 // GMRES with one classical Gram-Schmidt pass, both stopping on the FP64 true
@@ -31,17 +32,41 @@ namespace hdg {
 
 namespace {
 
-constexpr int SW = SMALL_THREADS / 64;   // wavefronts per workgroup
-static_assert(SW == 4 && SMALL_P1_DENSE <= 64, "the dense P1 phase: four wavefronts, a row per lane");
+// How a workgroup reads the operators (OL):
+//   OPS_LDS     staged in LDS; a thread takes whole facets (its patch values are
+//               read once for all rows), 256 threads.
+//   OPS_ROWS    from global memory (L2), one row of a facet per thread, the rows of
+//               one node in consecutive lanes, 512 threads: the rows' loads are what
+//               a phase waits for, and each wavefront waits for m times fewer of them.
+//   OPS_FACETS  from global memory, whole facets, 256 threads: p = 1, where a facet
+//               has two rows and the wider barriers cost more than the split gains.
+// Whole solve, rows / whole facets: 192 facets, p = 3, 13 right-hand sides (FGMRES)
+// 414 / 564 us (1024 threads 480: 128 registers spill), one (PCG) 253 / 284; p = 2,
+// FGMRES 337 / 360, 300 facets, PCG 310 / 400, 432 facets 390 / 435; 432 facets, p = 1,
+// 247 / 235.
+constexpr int OPS_FACETS = 0, OPS_LDS = 1, OPS_ROWS = 2;
+template <int OL>
+constexpr int NT = OL == OPS_ROWS ? SMALL_ROW_THREADS : SMALL_THREADS;   // threads per workgroup
+template <int OL>
+constexpr int SW = NT<OL> / 64;                                          // wavefronts per workgroup
+static_assert(SW<OPS_LDS> == 4 && SW<OPS_ROWS> >= 4 && SMALL_P1_DENSE <= 64,
+              "the dense P1 phase: four wavefronts, a row per lane");
 
-// The trace unknowns a thread owns: the m unknowns of facets tid, tid + SMALL_THREADS, ...
-// -- the items the facet kernels below write -- so that element-wise updates
-// read only values the same thread wrote (no barrier needed between them).
-template <int M, typename F>
+// The trace unknowns a thread owns -- the items the facet kernels below write --
+// so that element-wise updates read only values the same thread wrote (no
+// barrier needed between them).
+template <int M, int OL, typename F>
 __device__ __forceinline__ void for_own(int ne, F &&f) {
-    for (int e = threadIdx.x; e < ne; e += SMALL_THREADS)
+    if constexpr (OL != OPS_ROWS) {
+        for (int e = threadIdx.x; e < ne; e += NT<OL>)
 #pragma unroll
-        for (int a = 0; a < M; ++a) f(e * M + a);
+            for (int a = 0; a < M; ++a) f(e * M + a);
+    } else {
+        for (int i = threadIdx.x; i < ne * M; i += NT<OL>) {
+            const int a = i / ne;
+            f((i - a * ne) * M + a);
+        }
+    }
 }
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -52,13 +77,14 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 // Block-wide sum of one partial value per thread; every thread receives the
 // total (fixed summation order, so every thread holds the same bits).
+template <int OL>
 __device__ __forceinline__ double block_sum(double v, double *red) {
     const double s = wave_sum(v);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
     double t = 0.0;
 #pragma unroll
-    for (int q = 0; q < SW; ++q) t += red[q];
+    for (int q = 0; q < SW<OL>; ++q) t += red[q];
     return t;
 }
 
@@ -77,9 +103,9 @@ typedef __attribute__((address_space(3))) const int lds_int;
 typedef __attribute__((address_space(3))) const dbl2_t lds_double2;
 typedef __attribute__((address_space(3))) double lds_dbl;   // P1 level vectors (always in LDS)
 
-template <bool OL>
+template <int OL>
 __device__ __forceinline__ void opr2(const double *p, double (&o)[2]) {
-    if constexpr (OL) {
+    if constexpr (OL == OPS_LDS) {
         const dbl2_t v = *(const lds_double2 *)p;
         o[0] = v.x;
         o[1] = v.y;
@@ -87,14 +113,14 @@ __device__ __forceinline__ void opr2(const double *p, double (&o)[2]) {
         ld2(p, o);
     }
 }
-template <bool OL>
+template <int OL>
 __device__ __forceinline__ int opri(const int *p) {
-    if constexpr (OL) return *(const lds_int *)p;
+    if constexpr (OL == OPS_LDS) return *(const lds_int *)p;
     else return *p;
 }
-template <bool OL>
+template <int OL>
 __device__ __forceinline__ double oprd(const double *p) {
-    if constexpr (OL) return *(const lds_double *)p;
+    if constexpr (OL == OPS_LDS) return *(const lds_double *)p;
     else return *p;
 }
 
@@ -105,14 +131,59 @@ struct Ops {
     P1Lev lev[SMALL_LEVELS];
 };
 
+// One row of a facet's block row (global memory): sum over the J blocks of A_j[a][:] x_j,
+// in the order the whole-facet loops add in
+template <int M, int J, typename X>
+__device__ __forceinline__ double row_dot(const double *A, size_t NE, int e, int a, X &&x) {
+    double acc = 0.0;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        if constexpr (M % 2 == 0) {
+#pragma unroll
+            for (int h = 0; h < M / 2; ++h) {
+                double w[2];
+                ld2(A + ((size_t)((j * M + a) * (M / 2) + h) * NE + e) * 2, w);
+                acc += w[0] * x(j, 2 * h);
+                acc += w[1] * x(j, 2 * h + 1);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < M; ++k) {
+                const int c = (j * M + a) * M + k;
+                acc += A[((size_t)(c >> 1) * NE + e) * 2 + (c & 1)] * x(j, k);
+            }
+        }
+    }
+    return acc;
+}
+
+// the items of a thread in the row-wise phases
+template <int M, typename F>
+__device__ __forceinline__ void for_rows(int ne, F &&f) {
+    for (int i = threadIdx.x; i < ne * M; i += NT<OPS_ROWS>) {
+        const int a = i / ne;
+        f(i - a * ne, a);
+    }
+}
+
 // y = S x  (b == nullptr) or y = b - S x over this thread's facets; x in LDS
-template <int M, bool OL>
+template <int M, int OL>
 __device__ void s_apply(int ne, const Ops &O, const double *x, const double *b, double *y) {
+    if constexpr (OL == OPS_ROWS) {
+        for_rows<M>(ne, [&](int e, int a) {
+            int id[5] = {e};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) id[j + 1] = O.nbr[(size_t)j * ne + e];
+            const double s = row_dot<M, 5>(O.S, ne, e, a, [&](int j, int k) { return x[id[j] * M + k]; });
+            y[e * M + a] = b ? b[e * M + a] - s : s;
+        });
+        return;
+    }
     constexpr int C = 5 * M * M, G = padded(C, 2) / 2;
     const size_t NE = (size_t)ne;
     const double *S = O.S;
     const int *nbr = O.nbr;
-    for (int e = threadIdx.x; e < ne; e += SMALL_THREADS) {
+    for (int e = threadIdx.x; e < ne; e += NT<OL>) {
         int id[5];
         id[0] = e;
 #pragma unroll
@@ -141,15 +212,30 @@ __device__ void s_apply(int ne, const Ops &O, const double *x, const double *b, 
 // PCG direction and operator in one phase: pn = z + beta po at this thread's
 // facets and w = S pn, pn at the patch facets evaluated in place (the same
 // expression, so the same bits); returns this thread's part of pn . w
-template <int M, bool OL>
+template <int M, int OL>
 __device__ double s_apply_dir(int ne, const Ops &O, const double *z, double beta, const double *po, double *pn,
                               double *w) {
+    if constexpr (OL == OPS_ROWS) {
+        double part = 0.0;
+        for_rows<M>(ne, [&](int e, int a) {
+            int id[5] = {e};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) id[j + 1] = O.nbr[(size_t)j * ne + e];
+            const double s = row_dot<M, 5>(O.S, ne, e, a,
+                                           [&](int j, int k) { return z[id[j] * M + k] + beta * po[id[j] * M + k]; });
+            const double d = z[e * M + a] + beta * po[e * M + a];
+            pn[e * M + a] = d;
+            w[e * M + a] = s;
+            part += d * s;
+        });
+        return part;
+    }
     constexpr int C = 5 * M * M, G = padded(C, 2) / 2;
     const size_t NE = (size_t)ne;
     const double *S = O.S;
     const int *nbr = O.nbr;
     double part = 0.0;
-    for (int e = threadIdx.x; e < ne; e += SMALL_THREADS) {
+    for (int e = threadIdx.x; e < ne; e += NT<OL>) {
         int id[5];
         id[0] = e;
 #pragma unroll
@@ -186,7 +272,7 @@ __device__ double s_apply_dir(int ne, const Ops &O, const double *z, double beta
 }
 
 // omega D_f^-1 r_f at facet f (the multi-launch first sweep's arithmetic)
-template <int M, bool OL>
+template <int M, int OL>
 __device__ __forceinline__ void jacobi_at(const Ops &O, size_t NE, int f, const double *r, double (&z)[M]) {
     constexpr int C = M * M, G = padded(C, 2) / 2;
     const double *Dw = O.Dw;
@@ -209,7 +295,7 @@ __device__ __forceinline__ void jacobi_at(const Ops &O, size_t NE, int f, const 
 }
 
 // omega D_f^-1 rv for the values rv of facet f
-template <int M, bool OL>
+template <int M, int OL>
 __device__ __forceinline__ void jacobi_of(const Ops &O, size_t NE, int f, const double (&rv)[M], double (&z)[M]) {
     constexpr int C = M * M, G = padded(C, 2) / 2;
     const double *Dw = O.Dw;
@@ -227,23 +313,53 @@ __device__ __forceinline__ void jacobi_of(const Ops &O, size_t NE, int f, const 
     }
 }
 
+// y = the first damped sweep from z0 (already complete in LDS), by rows
+template <int M>
+__device__ void s_sweep_from_z0(int ne, const Ops &O, double omega, const double *z0, double *y) {
+    const SweepCoef cf{1.0 - omega, 1.0, 1.0, 0.0, nullptr, nullptr};
+    for_rows<M>(ne, [&](int e, int a) {
+        int id[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) id[j] = O.nbr[(size_t)j * ne + e];
+        const double s = row_dot<M, 4>(O.T, ne, e, a, [&](int j, int k) { return z0[id[j] * M + k]; });
+        const double z = z0[e * M + a];
+        y[e * M + a] = sweep_combine(cf, z, z, s);
+    });
+}
+
 // The PCG update fused with the first V-cycle phase of the next preconditioner
 // application: at this thread's facets lam += alpha p and rn = r - alpha w (into
 // a second buffer: the old r is still read at the patch facets), then z0 =
 // omega D^-1 rn and, with y != nullptr, the first sweep from zero, rn at the
 // patch facets evaluated in place (the same expression, so the same bits).
 // Returns this thread's part of rn . rn.
-template <int M, bool OL>
+template <int M, int OL>
 __device__ double s_update_first_sweep(int ne, const Ops &O, double omega, double alpha, const double *p,
                                        const double *w, const double *r, double *rn, double *lam, double *z0,
                                        double *y) {
+    if constexpr (OL == OPS_ROWS) {
+        double part = 0.0;
+        for_rows<M>(ne, [&](int e, int a) {
+            const int i = e * M + a;
+            const double v = r[i] - alpha * w[i];
+            rn[i] = v;
+            lam[i] += alpha * p[i];
+            part += v * v;
+            z0[i] = row_dot<M, 1>(O.Dw, ne, e, a, [&](int, int k) { return r[e * M + k] - alpha * w[e * M + k]; });
+        });
+        if (y) {
+            __syncthreads();
+            s_sweep_from_z0<M>(ne, O, omega, z0, y);
+        }
+        return part;
+    }
     constexpr int C = 4 * M * M, G = padded(C, 2) / 2;
     const size_t NE = (size_t)ne;
     const double *T = O.T;
     const int *nbr = O.nbr;
     const SweepCoef cf{1.0 - omega, 1.0, 1.0, 0.0, nullptr, nullptr};
     double part = 0.0;
-    for (int e = threadIdx.x; e < ne; e += SMALL_THREADS) {
+    for (int e = threadIdx.x; e < ne; e += NT<OL>) {
         double rv[M], zv[5][M];
 #pragma unroll
         for (int a = 0; a < M; ++a) {
@@ -290,14 +406,24 @@ __device__ double s_update_first_sweep(int ne, const Ops &O, double omega, doubl
 // z0 = omega D^-1 r at this thread's facets and, with y != nullptr, the first
 // damped block-Jacobi sweep from zero y = (1 - omega) z0 + z0 - sum_j T_j z0_j
 // (z0 at the patch facets computed in place)
-template <int M, bool OL>
+template <int M, int OL>
 __device__ void s_first_sweep(int ne, const Ops &O, double omega, const double *r, double *z0, double *y) {
+    if constexpr (OL == OPS_ROWS) {
+        for_rows<M>(ne, [&](int e, int a) {
+            z0[e * M + a] = row_dot<M, 1>(O.Dw, ne, e, a, [&](int, int k) { return r[e * M + k]; });
+        });
+        if (y) {
+            __syncthreads();
+            s_sweep_from_z0<M>(ne, O, omega, z0, y);
+        }
+        return;
+    }
     constexpr int C = 4 * M * M, G = padded(C, 2) / 2;
     const size_t NE = (size_t)ne;
     const double *T = O.T;
     const int *nbr = O.nbr;
     const SweepCoef cf{1.0 - omega, 1.0, 1.0, 0.0, nullptr, nullptr};
-    for (int e = threadIdx.x; e < ne; e += SMALL_THREADS) {
+    for (int e = threadIdx.x; e < ne; e += NT<OL>) {
         double zv[5][M];
         jacobi_at<M, OL>(O, NE, e, r, zv[0]);
 #pragma unroll
@@ -328,16 +454,43 @@ __device__ void s_first_sweep(int ne, const Ops &O, double omega, const double *
 
 // damped block-Jacobi sweep y = (1 - omega) x' + z0 - sum_j T_j x'_j, x' = x + pi qc;
 // returns this thread's part of d . y when d is given
-template <int M, bool OL>
+template <int M, int OL>
 __device__ double s_sweep(int ne, const Ops &O, double omega, const double *x, const double *z0, const lds_dbl *qc,
                           double *y, const double *d = nullptr) {
+    if constexpr (OL == OPS_ROWS) {
+        constexpr int P = M - 1;
+        const SweepCoef cf{1.0 - omega, 1.0, 1.0, 0.0, nullptr, nullptr};
+        double part = 0.0;
+        for_rows<M>(ne, [&](int e, int a) {
+            int id[5] = {e};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) id[j + 1] = O.nbr[(size_t)j * ne + e];
+            double q0[5] = {}, q1[5] = {};
+            if (qc)
+#pragma unroll
+                for (int j = 0; j < 5; ++j) {
+                    q0[j] = qc[O.fvert[2 * id[j]]];
+                    q1[j] = qc[O.fvert[2 * id[j] + 1]];
+                }
+            const double s = row_dot<M, 4>(O.T, ne, e, a, [&](int j, int k) {
+                const double v = x[id[j + 1] * M + k];
+                return qc ? v + p1_node<P>(k, q0[j + 1], q1[j + 1]) : v;
+            });
+            double xe = x[e * M + a];
+            if (qc) xe += p1_node<P>(a, q0[0], q1[0]);
+            const double v = sweep_combine(cf, xe, z0[e * M + a], s);
+            y[e * M + a] = v;
+            if (d) part += d[e * M + a] * v;
+        });
+        return part;
+    }
     double part = 0.0;
     const double *T = O.T;
     const int *nbr = O.nbr, *fvert = O.fvert;
     constexpr int P = M - 1, C = 4 * M * M, G = padded(C, 2) / 2;
     const size_t NE = (size_t)ne;
     const SweepCoef cf{1.0 - omega, 1.0, 1.0, 0.0, nullptr, nullptr};
-    for (int e = threadIdx.x; e < ne; e += SMALL_THREADS) {
+    for (int e = threadIdx.x; e < ne; e += NT<OL>) {
         int id[5];
         id[0] = e;
 #pragma unroll
@@ -382,12 +535,12 @@ __device__ double s_sweep(int ne, const Ops &O, double omega, const double *x, c
 // pi^T: rc[v] = sum over facet ends at v of sum_k w_end(k) res[e][k].  Four lanes
 // per vertex take every fourth facet end and add their sums by shuffles, so that
 // the whole workgroup shares the short per-vertex lists.
-template <int M, bool OL>
+template <int M, int OL>
 __device__ void s_restrict_trace(int nv, const Ops &O, const double *res, lds_dbl *rc) {
     constexpr int P = M - 1;
     const int *vf_row = O.vf_row, *vf_col = O.vf_col;
-    const int nvr = (nv + SMALL_THREADS / 4 - 1) / (SMALL_THREADS / 4) * (SMALL_THREADS / 4);   // uniform trip count
-    for (int v0 = 0; v0 < nvr; v0 += SMALL_THREADS / 4) {
+    const int nvr = (nv + NT<OL> / 4 - 1) / (NT<OL> / 4) * (NT<OL> / 4);   // uniform trip count
+    for (int v0 = 0; v0 < nvr; v0 += NT<OL> / 4) {
         const int v = v0 + (threadIdx.x >> 2), sub = threadIdx.x & 3;
         double acc = 0.0;
         if (v < nv) {
@@ -428,7 +581,7 @@ __device__ __forceinline__ double range_sum(int cnt, F &&f) {
     return s;
 }
 
-template <bool OL>
+template <int OL>
 __device__ __forceinline__ double s_p1_ax(const P1Lev &L, int v, const lds_dbl *x) {
     const double s = oprd<OL>(L.diag + v) * x[v];
     return s + range_sum(L.w, [&](int k) {
@@ -445,7 +598,7 @@ struct P1Vecs {
 
 // One P1 multigrid V-cycle from the finest level's right-hand side; returns the
 // LDS vector holding the result.
-template <bool OL>
+template <int OL>
 __device__ lds_dbl *s_p1_vcycle(int nlev, int nu, double w, const Ops &O, const P1Vecs *pv) {
     const int top = nlev - 1, tid = threadIdx.x;
     // after pre-smoothing the iterate is in x when the sweeps after the first
@@ -460,10 +613,10 @@ __device__ lds_dbl *s_p1_vcycle(int nlev, int nu, double w, const Ops &O, const 
         const lds_dbl *b = pv->b[l];
         auto dinv = [&](int v) { return oprd<OL>(L.dinv + v); };
         if (nu == 1) {
-            for (int v = tid; v < L.n; v += SMALL_THREADS) x[v] = w * dinv(v) * b[v];
+            for (int v = tid; v < L.n; v += NT<OL>) x[v] = w * dinv(v) * b[v];
         } else {
             // two sweeps from zero: x1 = w D^-1 b (evaluated where needed), x2 = x1 + w D^-1 (b - A x1)
-            for (int v = tid; v < L.n; v += SMALL_THREADS) {
+            for (int v = tid; v < L.n; v += NT<OL>) {
                 const double x1 = w * dinv(v) * b[v];
                 const double ax = oprd<OL>(L.diag + v) * x1 + range_sum(L.w, [&](int k) {
                     const int u = opri<OL>(L.col + (size_t)k * L.n + v);
@@ -474,17 +627,17 @@ __device__ lds_dbl *s_p1_vcycle(int nlev, int nu, double w, const Ops &O, const 
         }
         __syncthreads();
         for (int k = 2; k < nu; ++k) {
-            for (int v = tid; v < L.n; v += SMALL_THREADS) y[v] = x[v] + w * dinv(v) * (b[v] - s_p1_ax<OL>(L, v, x));
+            for (int v = tid; v < L.n; v += NT<OL>) y[v] = x[v] + w * dinv(v) * (b[v] - s_p1_ax<OL>(L, v, x));
             __syncthreads();
             lds_dbl *t = x;
             x = y;
             y = t;
         }
-        for (int v = tid; v < L.n; v += SMALL_THREADS) y[v] = b[v] - s_p1_ax<OL>(L, v, x);
+        for (int v = tid; v < L.n; v += NT<OL>) y[v] = b[v] - s_p1_ax<OL>(L, v, x);
         __syncthreads();
         const P1Lev &Cl = O.lev[l - 1];
         lds_dbl *bc = pv->b[l - 1];
-        for (int c = tid; c < Cl.n; c += SMALL_THREADS) {
+        for (int c = tid; c < Cl.n; c += NT<OL>) {
             const int k0 = opri<OL>(L.crow + c);
             bc[c] = range_sum(opri<OL>(L.crow + c + 1) - k0,
                               [&](int k) { return oprd<OL>(L.cw + k0 + k) * y[opri<OL>(L.ccol + k0 + k)]; });
@@ -495,7 +648,7 @@ __device__ lds_dbl *s_p1_vcycle(int nlev, int nu, double w, const Ops &O, const 
         const int n0 = O.lev[0].n;
         const lds_dbl *b0 = pv->b[0];
         lds_dbl *x0 = pv->x[0];
-        for (int i = tid; i < n0; i += SMALL_THREADS)
+        for (int i = tid; i < n0; i += NT<OL>)
             x0[i] = range_sum(n0, [&](int j) { return oprd<OL>(O.Ainv + (size_t)i * n0 + j) * b0[j]; });
         __syncthreads();
     }
@@ -504,7 +657,7 @@ __device__ lds_dbl *s_p1_vcycle(int nlev, int nu, double w, const Ops &O, const 
         lds_dbl *x = pre(l), *y = other(l);
         const lds_dbl *xc = fin(l - 1), *b = pv->b[l];
         for (int k = 0; k < nu; ++k) {
-            for (int v = tid; v < L.n; v += SMALL_THREADS) {
+            for (int v = tid; v < L.n; v += NT<OL>) {
                 auto xin = [&](int u) -> double {
                     double s = x[u];
                     if (k == 0)
@@ -542,7 +695,7 @@ struct SmallLds {
 };
 
 constexpr size_t small_fixed_doubles() {
-    return 2 * (SMALL_MAXR + 1) * SW + 4 * 64 + (SMALL_MAXR + 1) + (SMALL_MAXR + 1) * SMALL_MAXR + 3 * SMALL_MAXR +
+    return 2 * (SMALL_MAXR + 1) * SW<OPS_LDS> + 4 * 64 + (SMALL_MAXR + 1) + (SMALL_MAXR + 1) * SMALL_MAXR + 3 * SMALL_MAXR +
            (SMALL_MAXR + 1) + 8;
 }
 
@@ -567,7 +720,7 @@ __device__ SmallLds carve(const SmallArgs &A, Ops *ops, P1Vecs *pv, double *base
         q += 3 * n;
     }
     L.red = q;
-    q += 2 * (SMALL_MAXR + 1) * SW;
+    q += 2 * (SMALL_MAXR + 1) * SW<OPS_LDS>;
     L.dpart = q;
     q += 4 * 64;
     L.hv = q;
@@ -597,7 +750,7 @@ __device__ SmallLds carve(const SmallArgs &A, Ops *ops, P1Vecs *pv, double *base
 // z = V(r): r and z in LDS.  With d given, returns this thread's part of d . z and
 // leaves the barrier after the last sweep to the caller's reduction.
 // The V-cycle after its first phase (z0 and the first sweep from zero in L.z0, L.x).
-template <int M, bool OL>
+template <int M, int OL>
 __device__ double s_vcycle_rest(const SmallArgs &A, SmallLds &L, const double *r, double *z, const double *d) {
     const Ops &O = *L.ops;
     const int ne = A.ne, tid = threadIdx.x;
@@ -631,11 +784,11 @@ __device__ double s_vcycle_rest(const SmallArgs &A, SmallLds &L, const double *r
         lds_dbl *xv = L.pv->x[top];
         const int wv = tid >> 6, lane = tid & 63, jc = (nv + 3) / 4, j0 = wv * jc, j1 = min(nv, j0 + jc);
         double s = 0.0;
-        if (lane < nv) {
+        if (wv < 4 && lane < nv) {
 #pragma unroll 8
             for (int j = j0; j < j1; ++j) s += oprd<OL>(BT + (size_t)j * nv + lane) * bv[j];
         }
-        L.dpart[wv * 64 + lane] = s;
+        if (wv < 4) L.dpart[wv * 64 + lane] = s;
         __syncthreads();
         if (tid < nv) xv[tid] = (L.dpart[tid] + L.dpart[64 + tid]) + (L.dpart[128 + tid] + L.dpart[192 + tid]);
         __syncthreads();
@@ -664,7 +817,7 @@ __device__ double s_vcycle_rest(const SmallArgs &A, SmallLds &L, const double *r
     return part;
 }
 
-template <int M, bool OL>
+template <int M, int OL>
 __device__ double s_vcycle(const SmallArgs &A, SmallLds &L, const double *r, double *z, const double *d = nullptr) {
     s_first_sweep<M, OL>(A.ne, *L.ops, A.omega, r, L.z0, A.nu_pre >= 2 ? L.x : nullptr);
     __syncthreads();
@@ -701,8 +854,8 @@ __device__ void publish_image(const SmallArgs &A, Ops *ops, const char *c) {
     });
 }
 
-template <int P, bool STAGE, bool OL>
-__global__ __launch_bounds__(SMALL_THREADS) void k_solve_small(const SmallArgs A) {
+template <int P, bool STAGE, int OL>
+__global__ __launch_bounds__(NT<OL>) void k_solve_small(const SmallArgs A) {
     constexpr int M = P + 1, n = (P + 1) * (P + 2) / 2, nc = 3 * n, nt = 3 * M, ZW = cell_zw(P);
     extern __shared__ double lds[];
     __shared__ Ops sops;
@@ -736,13 +889,14 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_solve_small(const SmallArgs A
     const u4 *isrc = reinterpret_cast<const u4 *>(A.image);   // device allocations are 256-byte aligned
     u4 *idst = reinterpret_cast<u4 *>(L.img);
     u4 iv[IU];
+    if constexpr (OL == OPS_LDS)
 #pragma unroll
-    for (int u = 0; u < IU; ++u) {
-        const int i = tid + u * SMALL_THREADS;
-        if (i < n16) iv[u] = isrc[i];
-    }
+        for (int u = 0; u < IU; ++u) {
+            const int i = tid + u * NT<OL>;
+            if (i < n16) iv[u] = isrc[i];
+        }
     const size_t NK = (size_t)A.nk;
-    double *red0 = L.red, *red1 = L.red + (SMALL_MAXR + 1) * SW;
+    double *red0 = L.red, *red1 = L.red + (SMALL_MAXR + 1) * SW<OPS_LDS>;
     int rsel = 0;
     auto red = [&]() {   // alternate the reduction areas (a barrier always separates reuse)
         rsel ^= 1;
@@ -752,53 +906,59 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_solve_small(const SmallArgs A
     // ---- right-hand side of the trace system and the initial guess
     if (STAGE) {
         // Step 1: rhat = sum over the facet's two cells of C A^-1 (r, v)_K, row of the facet's node
-        for (int e = tid; e < ne; e += SMALL_THREADS) {
-#pragma unroll
-            for (int a = 0; a < M; ++a) {
-                double s = 0.0;
-                for (int side = 0; side < 2; ++side) {
-                    const int K = A.fcell[2 * e + side], i = A.floc[2 * e + side];
-                    const int row = loc_trace<P, 1>(i, a, side);
-                    double t = 0.0;
-                    for (int j = 0; j < nc; ++j) {
-                        const int idx = row * ZW + j;
-                        t += A.Zr[((size_t)(idx / 2) * NK + K) * 2 + idx % 2] * A.r_cell[((size_t)K * nc + j) * nb + rh];
-                    }
-                    s += t;
+        auto rhat_at = [&](int e, int a) {
+            double s = 0.0;
+            for (int side = 0; side < 2; ++side) {
+                const int K = A.fcell[2 * e + side], i = A.floc[2 * e + side];
+                const int row = loc_trace<P, 1>(i, a, side);
+                double t = 0.0;
+                for (int j = 0; j < nc; ++j) {
+                    const int idx = row * ZW + j;
+                    t += A.Zr[((size_t)(idx / 2) * NK + K) * 2 + idx % 2] * A.r_cell[((size_t)K * nc + j) * nb + rh];
                 }
-                L.b[e * M + a] = s;
-                L.lam[e * M + a] = 0.0;
+                s += t;
             }
+            L.b[e * M + a] = s;
+            L.lam[e * M + a] = 0.0;
+        };
+        if constexpr (OL == OPS_ROWS) {
+            for_rows<M>(ne, rhat_at);
+        } else {
+            for (int e = tid; e < ne; e += NT<OL>)
+#pragma unroll
+                for (int a = 0; a < M; ++a) rhat_at(e, a);
         }
     } else {
-        for_own<M>(ne, [&](int i) {
+        for_own<M, OL>(ne, [&](int i) {
             L.b[i] = A.rhat[(size_t)i * nb + rh];
             L.lam[i] = A.lam[(size_t)i * nb + rh];
         });
     }
-#pragma unroll
-    for (int u = 0; u < IU; ++u) {
-        const int i = tid + u * SMALL_THREADS;
-        if (i < n16) idst[i] = iv[u];
-    }
-    for (int i0 = tid + IU * SMALL_THREADS; i0 < n16; i0 += IU * SMALL_THREADS) {
+    if constexpr (OL == OPS_LDS) {
 #pragma unroll
         for (int u = 0; u < IU; ++u) {
-            const int i = i0 + u * SMALL_THREADS;
-            if (i < n16) iv[u] = isrc[i];
-        }
-#pragma unroll
-        for (int u = 0; u < IU; ++u) {
-            const int i = i0 + u * SMALL_THREADS;
+            const int i = tid + u * NT<OL>;
             if (i < n16) idst[i] = iv[u];
+        }
+        for (int i0 = tid + IU * NT<OL>; i0 < n16; i0 += IU * NT<OL>) {
+#pragma unroll
+            for (int u = 0; u < IU; ++u) {
+                const int i = i0 + u * NT<OL>;
+                if (i < n16) iv[u] = isrc[i];
+            }
+#pragma unroll
+            for (int u = 0; u < IU; ++u) {
+                const int i = i0 + u * NT<OL>;
+                if (i < n16) idst[i] = iv[u];
+            }
         }
     }
     __syncthreads();   // every thread has read the level sizes above
     if (L.img && tid == 0) publish_image(A, &sops, L.img);
     __syncthreads();
     double part = 0.0;
-    for_own<M>(ne, [&](int i) { part += L.b[i] * L.b[i]; });
-    const double bn2 = block_sum(part, red());
+    for_own<M, OL>(ne, [&](int i) { part += L.b[i] * L.b[i]; });
+    const double bn2 = block_sum<OL>(part, red());
     const double rtol = A.rtol;
     int its = 0, restarts = 0, status = HDG_OK;
     double rel = 0.0;
@@ -809,8 +969,8 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_solve_small(const SmallArgs A
         // true residual r = b - S lam (FP64)
         s_apply<M, OL>(ne, O, L.lam, L.b, L.r);
         part = 0.0;
-        for_own<M>(ne, [&](int i) { part += L.r[i] * L.r[i]; });
-        const double rr = block_sum(part, red());
+        for_own<M, OL>(ne, [&](int i) { part += L.r[i] * L.r[i]; });
+        const double rr = block_sum<OL>(part, red());
         rel = bn2 > 0 ? sqrt(rr / bn2) : sqrt(rr);
         if (!isfinite(rel)) {
             status = HDG_EBREAKDOWN;
@@ -827,7 +987,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_solve_small(const SmallArgs A
             // lam += alpha p, r -= alpha w, z = V(r), beta = r.z / rz
             // (the update of lam and r rides in the first phase of the next V-cycle;
             // r alternates between two buffers)
-            double rz = block_sum(s_vcycle<M, OL>(A, L, L.r, L.z, L.r), red());
+            double rz = block_sum<OL>(s_vcycle<M, OL>(A, L, L.r, L.z, L.r), red());
             double beta = 0.0;
             double *pbuf[2] = {L.p, L.p2};
             double *rc = L.r, *rnx = L.r2;
@@ -835,14 +995,14 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_solve_small(const SmallArgs A
             const double *po = L.z;   // first direction: z itself (beta = 0)
             while (its < A.maxit) {
                 double *pn = pbuf[pc];
-                const double pw = block_sum(s_apply_dir<M, OL>(ne, O, L.z, beta, po, pn, L.w), red());
+                const double pw = block_sum<OL>(s_apply_dir<M, OL>(ne, O, L.z, beta, po, pn, L.w), red());
                 const double alpha = rz / pw;
-                const double rrk = block_sum(s_update_first_sweep<M, OL>(ne, O, A.omega, alpha, pn, L.w, rc, rnx, L.lam,
+                const double rrk = block_sum<OL>(s_update_first_sweep<M, OL>(ne, O, A.omega, alpha, pn, L.w, rc, rnx, L.lam,
                                                                          L.z0, A.nu_pre >= 2 ? L.x : nullptr),
                                              red());
                 ++its;
                 if (!isfinite(rrk) || rrk <= rtol * rtol * bn2) break;
-                const double rzn = block_sum(s_vcycle_rest<M, OL>(A, L, rnx, L.z, rnx), red());
+                const double rzn = block_sum<OL>(s_vcycle_rest<M, OL>(A, L, rnx, L.z, rnx), red());
                 beta = rzn / rz;
                 rz = rzn;
                 po = pn;
@@ -857,7 +1017,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_solve_small(const SmallArgs A
             // vector also in LDS (L.p) as the V-cycle's input
             const int R = A.restart;
             const double beta = sqrt(rr);
-            for_own<M>(ne, [&](int i) {
+            for_own<M, OL>(ne, [&](int i) {
                 const double v = L.r[i] / beta;
                 Vb[i] = v;
                 L.p[i] = v;
@@ -868,36 +1028,38 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_solve_small(const SmallArgs A
             for (int j = 0; j < R && its < A.maxit; ++j) {
                 s_vcycle<M, OL>(A, L, L.p, L.z);
                 double *Zj = Zb + (size_t)j * ne * M;
-                for_own<M>(ne, [&](int i) { Zj[i] = L.z[i]; });
+                for_own<M, OL>(ne, [&](int i) { Zj[i] = L.z[i]; });
                 s_apply<M, OL>(ne, O, L.z, nullptr, L.w);
                 // h_q = V_q . w for q <= j
-                double *rd = red();
+                // (partials by wavefront; with more of them than the reduction area holds, in
+                // the V-cycle's x, x2 and res, which are consecutive and not in use here)
+                double *rd = OL == OPS_ROWS ? L.x : red();
                 for (int q = 0; q <= j; ++q) {
                     const double *Vq = Vb + (size_t)q * ne * M;
                     double s = 0.0;
-                    for_own<M>(ne, [&](int i) { s += Vq[i] * L.w[i]; });
+                    for_own<M, OL>(ne, [&](int i) { s += Vq[i] * L.w[i]; });
                     s = wave_sum(s);
-                    if ((tid & 63) == 0) rd[q * SW + (tid >> 6)] = s;
+                    if ((tid & 63) == 0) rd[q * SW<OL> + (tid >> 6)] = s;
                 }
                 __syncthreads();
                 if (tid <= j) {
                     double s = 0.0;
 #pragma unroll
-                    for (int q = 0; q < SW; ++q) s += rd[tid * SW + q];
+                    for (int q = 0; q < SW<OL>; ++q) s += rd[tid * SW<OL> + q];
                     L.hv[tid] = s;
                 }
                 __syncthreads();
                 part = 0.0;
-                for_own<M>(ne, [&](int i) {
+                for_own<M, OL>(ne, [&](int i) {
                     double wv = L.w[i];
                     for (int q = 0; q <= j; ++q) wv -= L.hv[q] * Vb[(size_t)q * ne * M + i];
                     L.w[i] = wv;
                     part += wv * wv;
                 });
-                const double hn = sqrt(block_sum(part, red()));
+                const double hn = sqrt(block_sum<OL>(part, red()));
                 double *Vn = Vb + (size_t)(j + 1) * ne * M;
                 const double inv = hn > 0 ? 1.0 / hn : 0.0;
-                for_own<M>(ne, [&](int i) {
+                for_own<M, OL>(ne, [&](int i) {
                     const double v = L.w[i] * inv;
                     Vn[i] = v;
                     L.p[i] = v;
@@ -938,7 +1100,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_solve_small(const SmallArgs A
                 }
             }
             __syncthreads();
-            for_own<M>(ne, [&](int i) {
+            for_own<M, OL>(ne, [&](int i) {
                 double s = L.lam[i];
                 for (int q = 0; q < k; ++q) s += L.y[q] * Zb[(size_t)q * ne * M + i];
                 L.lam[i] = s;
@@ -948,7 +1110,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_solve_small(const SmallArgs A
     }
 
     // ---- outputs: lam, (stage) the recovered cell fields, then the info record
-    for_own<M>(ne, [&](int i) { A.lam[(size_t)i * nb + rh] = L.lam[i]; });
+    for_own<M, OL>(ne, [&](int i) { A.lam[(size_t)i * nb + rh] = L.lam[i]; });
     if (STAGE) {
         __syncthreads();
         // Step 3: q = Ar r_cell - Wr lam_K per cell.  The cell's right-hand side is
@@ -956,7 +1118,11 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_solve_small(const SmallArgs A
         // together before its stores (which could alias them).
         constexpr int QG = 3;
         static_assert(nc % QG == 0, "three fields per node");
-        for (int K = tid; K < A.nk; K += SMALL_THREADS) {
+        // A cell's groups are one thread's; in the row-wise form one group each.
+        constexpr int GR = OL == OPS_ROWS ? 1 : nc / QG;
+        const int items = A.nk * (nc / QG / GR);
+        for (int it = tid; it < items; it += NT<OL>) {
+            const int K = OL == OPS_ROWS ? it % A.nk : it, g0 = OL == OPS_ROWS ? it / A.nk : 0;
             double l[nt], rc[nc];
 #pragma unroll
             for (int j = 0; j < nc; ++j) rc[j] = A.r_cell[((size_t)K * nc + j) * nb + rh];
@@ -967,7 +1133,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_solve_small(const SmallArgs A
 #pragma unroll
                 for (int t = 0; t < M; ++t) l[i * M + t] = L.lam[e * M + (rev ? P - t : t)];   // l[loc_trace(i, a, rev)] = lam[e][a]
             }
-            for (int a0 = 0; a0 < nc; a0 += QG) {
+            for (int a0 = g0 * QG; a0 < (g0 + GR) * QG; a0 += QG) {
                 double s[QG];
 #pragma unroll
                 for (int g = 0; g < QG; ++g) {
@@ -1007,16 +1173,20 @@ size_t small_lds_bytes(int ne, int m, const P1Lev *lev, int nlev, bool stage_ops
     return bytes;
 }
 
-template <int P, bool STAGE, bool OL>
+template <int P, bool STAGE, int OL>
 hipError_t prepare_one(size_t bytes) {
     return hipFuncSetAttribute((const void *)k_solve_small<P, STAGE, OL>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)bytes);
 }
 
+// operators in global memory: by rows from three unknowns per facet on
+template <int P>
+constexpr int OPS_GLOBAL = P == 1 ? OPS_FACETS : OPS_ROWS;
+
 template <int P>
 hipError_t prepare_p(size_t bytes) {
-    const hipError_t e[4] = {prepare_one<P, false, false>(bytes), prepare_one<P, false, true>(bytes),
-                             prepare_one<P, true, false>(bytes), prepare_one<P, true, true>(bytes)};
+    const hipError_t e[4] = {prepare_one<P, false, OPS_GLOBAL<P>>(bytes), prepare_one<P, false, OPS_LDS>(bytes),
+                             prepare_one<P, true, OPS_GLOBAL<P>>(bytes), prepare_one<P, true, OPS_LDS>(bytes)};
     for (hipError_t x : e)
         if (x != hipSuccess) return x;
     return hipSuccess;
@@ -1034,13 +1204,14 @@ hipError_t small_prepare(int p, size_t bytes) {
 
 template <int P>
 void launch_p(bool stage, const SmallArgs &A, size_t bytes, hipStream_t s) {
-    const dim3 grid(A.nb), block(SMALL_THREADS);
+    constexpr int G = OPS_GLOBAL<P>;
+    const dim3 grid(A.nb), block(A.stage_ops ? NT<OPS_LDS> : NT<G>);
     if (stage) {
-        if (A.stage_ops) k_solve_small<P, true, true><<<grid, block, bytes, s>>>(A);
-        else k_solve_small<P, true, false><<<grid, block, bytes, s>>>(A);
+        if (A.stage_ops) k_solve_small<P, true, OPS_LDS><<<grid, block, bytes, s>>>(A);
+        else k_solve_small<P, true, G><<<grid, block, bytes, s>>>(A);
     } else {
-        if (A.stage_ops) k_solve_small<P, false, true><<<grid, block, bytes, s>>>(A);
-        else k_solve_small<P, false, false><<<grid, block, bytes, s>>>(A);
+        if (A.stage_ops) k_solve_small<P, false, OPS_LDS><<<grid, block, bytes, s>>>(A);
+        else k_solve_small<P, false, G><<<grid, block, bytes, s>>>(A);
     }
 }
 
