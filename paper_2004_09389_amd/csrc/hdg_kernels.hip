@@ -529,6 +529,41 @@ __global__ __launch_bounds__(256) void k_trace_apply(int ne, int nb, const MT *_
     store_trace<M, NB1>(y, e * MB + r, nb, out);
 }
 
+// The same with one right-hand side and one row of a facet per thread, the rows of
+// one node in consecutive lanes (the launcher's rule says where).
+template <int M, typename MT, typename XT, typename YT, typename BT>
+__global__ __launch_bounds__(256) void k_trace_apply_row(int ne, const MT *__restrict__ S, const int *__restrict__ nbr,
+                                                         const XT *__restrict__ x, const BT *__restrict__ b,
+                                                         YT *__restrict__ y) {
+    using AT = typename Acc<MT>::type;
+    constexpr int V = Wide<MT>::V, W = M % 4 == 0 && V >= 4 ? 4 : M % 2 == 0 ? 2 : 1;   // row entries per load
+    typedef MT vec __attribute__((ext_vector_type(W)));
+    const int t = xcd_block() * blockDim.x + threadIdx.x;
+    if (t >= ne * M) return;
+    const int a = t / ne, e = t - a * ne;
+    const size_t NE = (size_t)ne;
+    int id[5] = {e};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) id[j + 1] = nbr[j * NE + e];
+    AT w[5][M];
+#pragma unroll
+    for (int j = 0; j < 5; ++j)
+#pragma unroll
+        for (int k = 0; k < M; k += W) {
+            const int c = (j * M + a) * M + k;
+            const vec v = __builtin_nontemporal_load(reinterpret_cast<const vec *>(S + ((size_t)(c / V) * NE + e) * V + c % V));
+#pragma unroll
+            for (int q = 0; q < W; ++q) w[j][k + q] = v[q];
+        }
+    AT acc = 0;
+#pragma unroll
+    for (int j = 0; j < 5; ++j)
+#pragma unroll
+        for (int k = 0; k < M; ++k) acc += w[j][k] * (AT)x[(size_t)id[j] * M + k];
+    const size_t o = (size_t)e * M + a;
+    y[o] = (YT)(b ? (double)b[o] - (double)acc : (double)acc);
+}
+
 // z0 = omega D^-1 r  (first sweep from a zero guess).  With scale != nullptr
 // the input is r / scale[rhs], and the scaled input is also written to rs
 // (normalisation of a Krylov basis vector fused into its first use).
@@ -2456,6 +2491,13 @@ static RowShape sweep_shape(int M, int ne, int nb, int rhs_block, int vb) {
     switch (M) { case 2: X(2); break; case 3: X(3); break; case 4: X(4); break; case 6: X(6); break; case 8: X(8); break; }
 #define M_SWITCH_RB(X) switch (M) { case 2: X(2); break; case 3: X(3); break; case 4: X(4); break; }
 
+// One row per thread pays where a facet's block row is long (6 or 8 unknowns,
+// Lax-Friedrichs) and one thread per facet is a wavefront or less per SIMD: 1728 facets,
+// m = 6 7.6 -> 4.1 us, 9408: 11.3 -> 4.6 (m = 8: 19.9 -> 10.3); 49152 facets 15.2 / 24.7
+// (each row gathers the patch again).  With m <= 4 the chain is short: 9408 facets,
+// m = 3 2.8 / 3.2 us, m = 4 3.4 / 3.3.
+static bool rowwise(int M, int ne) { return M >= 6 && (int64_t)ne * M <= 2 * SIMD_LANES; }
+#define M_SWITCH_ROW(X) switch (M) { case 6: X(6); break; case 8: X(8); break; }
 template <typename MT, typename XT, typename YT>
 void launch_trace_apply(int M, int ne, int nb, const MT *S, const int *nbr, const XT *x, const YT *b, YT *y,
                         hipStream_t s, int rhs_block) {
@@ -2468,6 +2510,12 @@ void launch_trace_apply(int M, int ne, int nb, const MT *S, const int *nbr, cons
     if constexpr (sizeof(XT) == 4) ROWS_LAUNCH(h, (k_trace_apply_rb<MM, MT, XT, YT, 4, 64, YT>), 4, 64, ne, nb, S, nbr, x, b, y)
         M_SWITCH_RB(TAB)
 #undef TAB
+        return;
+    }
+    if (nb == 1 && rowwise(M, ne)) {
+#define TR(MM) hipLaunchKernelGGL((k_trace_apply_row<MM, MT, XT, YT, YT>), GRID8(ne * M, 256), 0, s, ne, S, nbr, x, b, y)
+        M_SWITCH_ROW(TR)
+#undef TR
         return;
     }
 #define TA(MM)                                                                                          \
@@ -2488,6 +2536,12 @@ void launch_trace_residual_f32(int M, int ne, int nb, const double *S, const int
     ROWS_LAUNCH(h, (k_trace_apply_rb<MM, double, double, float, 2, 32, double>), 2, 32, ne, nb, S, nbr, x, b, y)
         M_SWITCH_RB(TAB)
 #undef TAB
+        return;
+    }
+    if (nb == 1 && rowwise(M, ne)) {
+#define TR(MM) hipLaunchKernelGGL((k_trace_apply_row<MM, double, double, float, double>), GRID8(ne * M, 256), 0, s, ne, S, nbr, x, b, y)
+        M_SWITCH_ROW(TR)
+#undef TR
         return;
     }
 #define TA(MM)                                                                                          \
