@@ -42,7 +42,7 @@ def parse():
     ap.add_argument("--n", type=int, default=256)
     ap.add_argument("--nrhs", type=int, default=1)
     ap.add_argument("--coarse", type=int, default=32, help="side of the coarsest P1 level")
-    ap.add_argument("--tail-max", type=int, default=0, help="P1 levels up to this size run in one workgroup")
+    ap.add_argument("--tail-max", type=int, default=0, help="P1 levels up to this size run as one dense product")
     ap.add_argument("--p1-nu", type=int, default=2, help="P1 Jacobi sweeps per level (pre and post)")
     ap.add_argument("--rtol", type=float, default=1e-8)
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle baseline")
