@@ -2033,7 +2033,7 @@ __global__ __launch_bounds__(256) void k_lincomb4(int64_t n, int nb, int nd, con
 // x = B b with B the dense map of a coarse level: the inverse of the coarsest
 // operator, or a whole V-cycle below a level collapsed into one matrix.  B
 // (8 n^2 bytes, row-major, rows padded to dense_ld(n) entries with zeros, the
-// row count to a multiple of 16) is read once per call and is the cost.
+// row count to a multiple of 48) is read once per call and is the cost.
 //
 // One right-hand side: one block per row, 16-byte loads, a butterfly in each
 // wavefront, then the four wavefronts in order (1024 rows 4.1 us, 2562 rows 11.4 us
@@ -2048,7 +2048,7 @@ __global__ __launch_bounds__(256) void k_lincomb4(int64_t n, int nb, int nd, con
 // columns in a sum is free, and A and B use the same one) and the four results are
 // added by two shuffles.  The wavefronts' sums are added through LDS in order:
 // repeated products are bitwise equal.  1024 rows: 4.0 us at 16 right-hand sides, 4.9 us at
-// 6; 2562 rows, where the 52 MB of B bound it: 16.0, 17.8 and (32) 22.7 us; the
+// 6; 2562 rows, where the 52 MB of B bound it, about 15.6 us at 6 (17.8 on 161 blocks); the
 // 784-vertex level of the 56x56 torus and those below it 5.2 us, 74 us in one workgroup.
 // Small row tiles because the matrix cores of a CU are the limit up to about 1100 rows
 // (642 rows, 16 right-hand sides: 4.6 us, with 16 x 16 tiles on 41 CUs 6.2 us).  Splitting the
@@ -2708,17 +2708,22 @@ void launch_p1_resid_restrict(int n, int W, const int *col, const double *val, c
 }
 #undef P1_GRID
 int dense_ld(int n) { return (n + 1) / 2 * 2; }
-size_t dense_doubles(int n) { return (size_t)((n + 15) / 16 * 16) * dense_ld(n); }
+size_t dense_doubles(int n) { return (size_t)((n + 47) / 48 * 48) * dense_ld(n); }   // whole blocks of 4, 8, 12 or 16 rows
 void launch_dense(const DenseMap &D, int nb, const double *b, double *x, hipStream_t s, bool f32) {
     const int n = D.n, ld = dense_ld(n);
-    // sixteen rows per block above 1100 rows, where B bounds the product and every block re-reads
-    // b (2562 rows, 6 / 32 right-hand sides: 17.8 / 22.7 us, four rows 22 / 26 us); four below,
-    // where more would leave CUs idle (1024 rows, 16: four 4.0 us, eight 5.3 us)
+    // Rows per block: as many blocks as CUs, and no more rows than that takes (1100 rows
+    // belong to the first line: 1024 rows, 16 right-hand sides: four 4.0 us, eight 5.3 us).
+    // V-cycle with 4 R rows for R = 2 / 3 / 4: 1600 rows, 6 right-hand sides 49.2 / - / 53.6 us,
+    // 1936 rows, 4: 49.8 / - / 53.5; 2562 rows, 6: 65.3 / 61.0 / 63.4, 2: 53.6 / 50.9 / 52.9.
 #define DN(R, T) hipLaunchKernelGGL((k_dense<R, T, VT>), dim3((n + 4 * R - 1) / (4 * R)), dim3(64 * DENSE_WAVES), 0, s, n, \
                                     ld, nb, D.B, pv<VT>(b), pv<VT>(x))
+#define DNT(R) if (nb <= 16) DN(R, 1); else if (nb <= 32) DN(R, 2); else DN(R, 4)
     P1_TYPED(if (nb == 1) hipLaunchKernelGGL(k_dense_row<VT>, dim3(n), dim3(256), 0, s, n, ld, D.B, pv<VT>(b), pv<VT>(x));
-             else if (n <= 1100) { if (nb <= 16) DN(1, 1); else if (nb <= 32) DN(1, 2); else DN(1, 4); }
-             else if (nb <= 16) DN(4, 1); else if (nb <= 32) DN(4, 2); else DN(4, 4))
+             else if (n <= 1100) { DNT(1); }
+             else if (n <= 2048) { DNT(2); }
+             else if (n <= 3072) { DNT(3); }
+             else { DNT(4); })
+#undef DNT
 #undef DN
 }
 void launch_dense_cols(int n, int col0, int ncol, const double *src, double *B, hipStream_t s) {

@@ -22,7 +22,9 @@ def _rel(a, b):
     (5, 5, 4096),     # 25 rows
     (12, 3, 4096),    # three levels collapsed into 144 rows
     (12, 3, 50),      # two of them (36 rows) below the finest level's own kernels
-    (44, 11, 4096),   # 1936 rows: more chunks than one run per wavefront
+    (44, 11, 4096),   # 1936 rows: more chunks than one run per wavefront; 8 rows a block
+    (49, 49, 0),      # 2401 rows (odd): 12 rows a block, ragged last one
+    (50, 25, 4096),   # 2500 rows, collapsed
 ])
 @pytest.mark.parametrize("nb", [1, 2, 16, 17, 32, 33, 64])
 def test_collapsed_levels_match_oracle(n, coarse, tail, nb):
