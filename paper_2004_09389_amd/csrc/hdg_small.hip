@@ -854,8 +854,14 @@ __device__ void publish_image(const SmallArgs &A, Ops *ops, const char *c) {
     });
 }
 
+// Whole facets from global memory: told that more than two wavefronts per SIMD are of no use,
+// the compiler keeps 233 registers and the loads in flight that they hold (163 without:
+// stage on a one-level 12 x 12 torus, f = 1, 346 us against 329).
+template <int OL>
+constexpr int MAX_WAVES = OL == OPS_FACETS ? 2 : 8;
+
 template <int P, bool STAGE, int OL>
-__global__ __launch_bounds__(NT<OL>) void k_solve_small(const SmallArgs A) {
+__global__ __launch_bounds__(NT<OL>) __attribute__((amdgpu_waves_per_eu(1, MAX_WAVES<OL>))) void k_solve_small(const SmallArgs A) {
     constexpr int M = P + 1, n = (P + 1) * (P + 2) / 2, nc = 3 * n, nt = 3 * M, ZW = cell_zw(P);
     extern __shared__ double lds[];
     __shared__ Ops sops;
