@@ -1817,7 +1817,10 @@ extern "C" int hdg_solve(hdg_ctx *c, int32_t nb, const double *rhat, double *lam
         HDG_REQUIRE(rhat && lam && rhat != lam, "rhat and lam must be distinct non-NULL buffers");
         check_aligned(rhat, "rhat");
         check_aligned(lam, "lam");
-        status = solve_impl(c, nb, rhat, lam, info, as_stream(stream));
+        hipStream_t s = as_stream(stream);
+        status = solve_impl(c, nb, rhat, lam, info, s);
+        // the loop ends when the last norm arrives: what its kernel still does, and PCG's copy of lam, follow
+        if (!use_small(c, krylov_kind(c))) HDG_HIP_CHECK(hipStreamSynchronize(s));
     });
     if (rc != HDG_OK) return rc;
     if (status == HDG_EBREAKDOWN) hdg::set_error("non-finite residual in the Krylov solve");
