@@ -845,18 +845,20 @@ int solve_fgmres(hdg_ctx *c, int nb, int vc_prec, int op_prec, double inner_eta,
                 if (!std::isfinite(h[r])) return true;   // stop the cycle; the true residual reports it
                 if (!(h[r] <= target(r))) all = false;
             }
-            if (all) return true;
-            // learned smoother judged by the mean residual reduction per iteration over this
-            // restart cycle; block-Jacobi takes over for the rest of the solve when it is too weak
-            if (c->use_mlp_now && i >= 1) {
-                for (int r = 0; r < nb; ++r)
-                    if (cyc0[r] > 0 && std::pow(h[r] / cyc0[r], 1.0 / (i + 1)) > c->opt.fallback_ratio) {
-                        c->use_mlp_now = false;
-                        ++fallbacks;
-                        break;
-                    }
-            }
-            return false;
+            return all;
+        };
+        // learned smoother judged by the mean residual reduction per iteration over this
+        // restart cycle (column i's estimate, in last); block-Jacobi takes over for the rest of the
+        // solve when it is too weak.  Asked once column i + 1 is queued, however early the
+        // estimate was looked at, so that it acts from column i + 2 on in every case.
+        auto judge = [&](int i) {
+            if (!c->use_mlp_now || i < 1) return;
+            for (int r = 0; r < nb; ++r)
+                if (cyc0[r] > 0 && std::pow(last[r] / cyc0[r], 1.0 / (i + 1)) > c->opt.fallback_ratio) {
+                    c->use_mlp_now = false;
+                    ++fallbacks;
+                    return;
+                }
         };
         // whether column seen + 1 is likely to end the cycle
         auto near_end = [&] {
@@ -910,6 +912,7 @@ int solve_fgmres(hdg_ctx *c, int nb, int vc_prec, int op_prec, double inner_eta,
                 k = j;   // column j was queued speculatively; the solution uses columns 0..j-1
                 break;
             }
+            judge(j - 1);
             if (near_end() && examine(j)) break;
         }
         hdg::launch_gmres_solve(nb, k, R, c->gm, c->hy, s);
