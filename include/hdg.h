@@ -437,9 +437,10 @@ int hdg_mlp_train(hdg_ctx *ctx, int32_t nrhs, const double *e0, int32_t cycles, 
  * Launch shapes that do not change results.  hdg_autotune times each
  * candidate on the context's own mesh at nrhs right-hand sides (HIP events,
  * a few launches each, on the stream) and keeps the fastest; hdg_set_tuning
- * imposes values.  Both drop the captured graphs.  Synchronous.  At nrhs >= 2
- * hdg_autotune allocates two cell arrays of nrhs columns for its timing and
- * frees them before it returns (HDG_EHIP if the allocation fails). */
+ * imposes values.  Both drop the captured graphs.  Synchronous.  Where cell_cells
+ * matters at nrhs, hdg_autotune allocates two cell arrays of nrhs columns for its
+ * timing and frees them before it returns (HDG_EHIP if the allocation fails);
+ * elsewhere it leaves cell_cells at 0. */
 typedef struct {
     int32_t mlp_samples_per_lane; /* samples (facet, rhs) each lane gathers in the learned
                                      smoothing kernel: 1 or 2 (default 1), or 4 = four consecutive
@@ -450,10 +451,13 @@ typedef struct {
                                    the mesh are large enough, the block's facet rows are staged in
                                    LDS and P1 threads take four right-hand sides (default 4); the
                                    results are the same bit for bit */
-    int32_t cell_cells;         /* cells per block of the batched condensation and recovery
-                                   kernels (nrhs >= 2; a block is cells x nrhs threads): 0 = the
-                                   most that fit in 256 threads and 64 KiB of staged rows (default),
-                                   1..32 = at most that many (larger values are clamped) */
+    int32_t cell_cells;         /* cells per block of the condensation and recovery kernels that stage
+                                   rows of dense cell maps (a block is cells x nrhs threads): both with
+                                   the Lax-Friedrichs flux, the condensation alone with the upwind flux
+                                   where f varies inside the cells (sphere, omega != 0), each above 3, 5
+                                   or 8 right-hand sides at p = 1, 2 or 3; no other kernel reads it.
+                                   0 = the most that fit in 256 threads and 64 KiB of staged rows
+                                   (default), 1..32 = at most that many (larger values are clamped) */
 } hdg_tuning;
 int hdg_get_tuning(const hdg_ctx *ctx, hdg_tuning *out);
 int hdg_set_tuning(hdg_ctx *ctx, const hdg_tuning *tuning);

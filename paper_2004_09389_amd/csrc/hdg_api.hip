@@ -2159,10 +2159,10 @@ extern "C" int hdg_autotune(hdg_ctx *c, int32_t nb, hdg_tuning *chosen, void *st
             }
         }
         c->rhs_block = best_rb;
-        // batched cell kernels (condensation, recovery): the most cells per block
-        // that fit, half or a quarter of them
+        // staged-row cell kernels: the most cells per block that fit, half or a quarter of
+        // them (other batches and fluxes do not take these kernels: the default)
         int best_cc = 0;
-        if (nb >= 2 && (c->flux == HDG_FLUX_LF || c->cf.zt)) {
+        if (nb > hdg::cell_small_dense(c->p) && (c->flux == HDG_FLUX_LF || c->cf.zt)) {
             const size_t cell_bytes = sizeof(double) * (size_t)c->n_cell * c->nc * nb;
             struct Scratch {   // freed on every way out, errors included
                 double *p = nullptr;

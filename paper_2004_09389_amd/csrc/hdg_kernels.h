@@ -212,6 +212,11 @@ size_t dense_doubles(int n);                    // entries of B, padding include
 void launch_dense_cols(int n, int col0, int ncol, const double *src, double *B, hipStream_t s);
 void launch_unit_cols(int n, int col0, int ncol, double *b, hipStream_t s);
 
+// Up to this many right-hand sides at degree p the dense maps are read per thread; above, staged
+// rows serve a whole batch.  Condensation on the level-6 sphere, per thread / staged: p = 3 at
+// 2, 4, 8 right-hand sides 57 / 376, 77 / 227, 126 / 175 us; p = 2 at 4, 5, 6, 8
+// 43 / 56, 54 / 55, 58 / 54, 70 / 63 us; p = 1 at 4, 6, 8 23 / 22, 30 / 25, 38 / 29 us.
+__host__ __device__ constexpr int cell_small_dense(int p) { return p == 3 ? 8 : (p == 2 ? 5 : 3); }
 // Cell passes by dense maps: condensation of the Lax-Friedrichs form and of the upwind form
 // where f varies inside the cells; recovery of the Lax-Friedrichs form and the DG baseline's
 // stage operator.  cells: cells per block of the batched (staged-row) kernels; 0 =

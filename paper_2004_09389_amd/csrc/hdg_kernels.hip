@@ -869,11 +869,6 @@ __global__ void k_p1_restrict(int nc, int nb, const int *__restrict__ crow, cons
 
 // loc[rho][K][r] = sum_j Zr[rho][j][K] r_cell[K][j][r]   (Step 1, cell part)
 constexpr int RECOVER_TILE = 128;   // threads per block of the small-batch cell kernels
-// Up to this many right-hand sides at degree p the dense maps are read per thread; above, staged
-// rows serve a whole batch.  Condensation on the level-6 sphere, per thread / staged: p = 3 at
-// 2, 4, 8 right-hand sides 57 / 376, 77 / 227, 126 / 175 us; p = 2 at 4, 5, 6, 8
-// 43 / 56, 54 / 55, 58 / 54, 70 / 63 us; p = 1 at 4, 6, 8 23 / 22, 30 / 25, 38 / 29 us.
-__host__ __device__ constexpr int cell_small_dense(int p) { return p == 3 ? 8 : (p == 2 ? 5 : 3); }
 
 // Condensation by the dense map at up to cell_small_dense(P) right-hand sides: one thread per
 // (cell, right-hand side), right-hand side fastest.  The block's cells read their inputs
