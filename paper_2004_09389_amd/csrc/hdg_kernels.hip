@@ -134,6 +134,17 @@ __global__ __launch_bounds__(64) void k_cell_condense(int nk, const double *__re
         }
     }
     const double kap = cp.kappa, tau = cp.tau, dt = cp.dt;
+    if constexpr (NU == 1) {   // written here, so that the elimination need not keep the geometry
+        if (geo && live && det_ok && r == 0) {
+            const double kd = kap / det;
+            const double v[CELL_GEO] = {kap * J00, kap * J01, kap * J10, kap * J11,
+                                        kd * L[0] * nx[0], kd * L[0] * ny[0], kd * L[1] * nx[1], kd * L[1] * ny[1],
+                                        kd * L[2] * nx[2], kd * L[2] * ny[2], kd * tau * L[0], kd * tau * L[1],
+                                        kd * tau * L[2], det / kap};
+#pragma unroll
+            for (int q = 0; q < CELL_GEO; ++q) geo[((size_t)(q / 2) * nk + K) * 2 + q % 2] = v[q];
+        }
+    }
     for (int q = r; q < nq; q += 32) {
         double f = cp.f0;
         if (cp.geom == HDG_SPHERE && cp.omega != 0.0) {
@@ -295,25 +306,19 @@ __global__ __launch_bounds__(64) void k_cell_condense(int nk, const double *__re
     if constexpr (NU == 1) {
         // the factors of the cell passes: Sigma^-1 M is the depth block of A^-1 Mtilde (fs_rows: its depth rows, padded to pairs)
         if (fs && ok && myk >= 0 && myk < n) {
+            // No early way out of the loop: it would stay rolled, index a[] at run time and so move
+            // the row to scratch memory (256x256 torus, p = 3: 8.8 ms; as it stands 2.7 ms)
+            const int ld = fs_rows ? (nc + 1) / 2 * 2 : n;
 #pragma unroll
-            for (int b = 0; b < nc; ++b) {
-                if (b >= (fs_rows ? nc : n)) break;
-                const int idx = fs_rows ? myk * ((nc + 1) / 2 * 2) + b : myk * n + b;
-                fs[((size_t)(idx / 2) * NK + K) * 2 + idx % 2] = (b < n ? ih : 1.0) * (myip * a[nc + nt + b]);
-            }
+            for (int b = 0; b < nc; ++b)
+                if (b < n || fs_rows) {
+                    const int idx = myk * ld + b;
+                    fs[((size_t)(idx / 2) * NK + K) * 2 + idx % 2] = (b < n ? ih : 1.0) * (myip * a[nc + nt + b]);
+                }
             if (fs_rows ? nc % 2 != 0 : n * n % 2 && myk == 0) {   // the padding entry
                 const int idx = fs_rows ? myk * (nc + 1) + nc : n * n;
                 fs[((size_t)(idx / 2) * NK + K) * 2 + idx % 2] = 0.0;
             }
-        }
-        if (geo && ok && r == 0) {
-            const double kd = kap / det;
-            const double v[CELL_GEO] = {kap * J00, kap * J01, kap * J10, kap * J11,
-                                        kd * L[0] * nx[0], kd * L[0] * ny[0], kd * L[1] * nx[1], kd * L[1] * ny[1],
-                                        kd * L[2] * nx[2], kd * L[2] * ny[2], kd * tau * L[0], kd * tau * L[1],
-                                        kd * tau * L[2], det / kap};
-#pragma unroll
-            for (int q = 0; q < CELL_GEO; ++q) geo[((size_t)(q / 2) * NK + K) * 2 + q % 2] = v[q];
         }
     }
     if (Ar && ok && myk >= 0) {
@@ -326,7 +331,7 @@ __global__ __launch_bounds__(64) void k_cell_condense(int nk, const double *__re
 #pragma unroll
     for (int rho = 0; rho < NR; ++rho) {
         const int lo = rho * XB, hi = lo + XB < NX ? lo + XB : NX;
-        if (lo >= nt && !Zr) break;   // the remaining columns are C A^-1 Mtilde alone
+        if (lo >= nt && !Zr) continue;   // the remaining columns are C A^-1 Mtilde alone
         __syncthreads();
         if (myk >= 0) {
 #pragma unroll
