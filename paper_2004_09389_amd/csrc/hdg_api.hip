@@ -1321,11 +1321,6 @@ void setup_impl(const hdg_mesh *levels, int nlev, const int32_t *const *parents,
         if (opt.persistent && nv <= hdg::SMALL_P1_DENSE) p1B = hdg::p1_vcycle_matrix(ops, parents, opt.p1_nu, opt.p1_omega);
     }
 
-    // ---- the small P1 levels as one dense product (no P1 hierarchy with the LF flux)
-    if (!c->lev.empty())
-        c->p1_dense = hdg::collapse_p1(c, c->lev, c->coarse_inv, hdg::p1_collapse_max(c),
-                                       opt.p1_nu, opt.p1_omega);
-
     // ---- work vectors
     const size_t vl = (size_t)ne * m * mr;
     c->vz0 = dev_alloc<double>(c, vl);
@@ -1341,9 +1336,19 @@ void setup_impl(const hdg_mesh *levels, int nlev, const int32_t *const *parents,
     const int Rr = opt.restart;
     const bool need_gmres = !(opt.krylov == HDG_KRYLOV_PCG);
     if (need_gmres) {
-        c->kV = dev_alloc<double>(c, (size_t)basis_slot(c) * (Rr + 1));
+        c->kV_len = (size_t)basis_slot(c) * (Rr + 1);
+        c->kV = dev_alloc<double>(c, c->kV_len);
         c->kZ = dev_alloc<double>(c, (size_t)basis_slot(c) * Rr);
     }
+    // ---- the small P1 levels as one dense product (no P1 hierarchy with the LF flux)
+    if (!p1B.empty() && nv <= hdg::p1_collapse_max(c)) {
+        c->p1_dense.map = hdg::make_dense(c, nv, p1B);   // the whole hierarchy, already at hand
+        c->p1_dense.top = (int)c->lev.size() - 1;
+    } else if (!c->lev.empty()) {
+        c->p1_dense = hdg::collapse_p1(c, c->lev, c->coarse_inv, hdg::p1_collapse_max(c),
+                                       opt.p1_nu, opt.p1_omega);
+    }
+
     c->red_blocks = 2048;   // upper bound of red_grid() for any nrhs
     c->red = dev_alloc<double>(c, (size_t)c->red_blocks * (Rr + 1) * mr);
     c->red2 = dev_alloc<double>(c, (size_t)c->red_blocks * mr);
@@ -1561,10 +1566,8 @@ int hdg::p1_collapse_max(const hdg_ctx *c) {
     return std::min(c->opt.p1_tail_max, std::clamp((int)fit, P1_COLLAPSE_MIN, P1_COLLAPSE_MAX));
 }
 
-constexpr int COLLAPSE_COLS = 64;   // unit vectors per pass of collapse_p1
-
 double *hdg::p1_cycle(std::vector<hdg::P1LevelDev> &lev, const hdg::P1Dense &dense, int l, int nb, int nu, double w,
-                      hipStream_t s) {
+                      hipStream_t s, int rb) {
     hdg::P1LevelDev &L = lev[l];
     if (l == dense.top) {
         hdg::launch_dense(dense.map, nb, L.b, L.x, s);
@@ -1572,68 +1575,100 @@ double *hdg::p1_cycle(std::vector<hdg::P1LevelDev> &lev, const hdg::P1Dense &den
     }
     double *x = L.x, *y = L.y;
     if (nu == 1) {
-        hdg::launch_p1_first(L.n, nb, L.dinv, w, L.b, x, s);
+        hdg::launch_p1_first(L.n, nb, L.dinv, w, L.b, x, s, false, rb);
     } else {
-        hdg::launch_p1_pre2(L.n, L.w, nb, L.col, L.val, L.diag, L.dinv, w, L.b, x, s);
+        hdg::launch_p1_pre2(L.n, L.w, nb, L.col, L.val, L.diag, L.dinv, w, L.b, x, s, false, rb);
         for (int k = 2; k < nu; ++k) {
-            hdg::launch_p1_sweep(L.n, L.w, nb, L.col, L.val, L.diag, L.dinv, w, L.b, x, nullptr, nullptr, y, s);
+            hdg::launch_p1_sweep(L.n, L.w, nb, L.col, L.val, L.diag, L.dinv, w, L.b, x, nullptr, nullptr, y, s,
+                                 false, rb);
             std::swap(x, y);
         }
     }
-    hdg::launch_p1_resid(L.n, L.w, nb, L.col, L.val, L.diag, L.b, x, y, s);
+    hdg::launch_p1_resid(L.n, L.w, nb, L.col, L.val, L.diag, L.b, x, y, s, false, rb);
     hdg::P1LevelDev &C = lev[l - 1];
-    hdg::launch_p1_restrict(C.n, nb, L.crow, L.ccol, L.cw, y, C.b, s);
-    const double *xc = hdg::p1_cycle(lev, dense, l - 1, nb, nu, w, s);
+    hdg::launch_p1_restrict(C.n, nb, L.crow, L.ccol, L.cw, y, C.b, s, false, rb);
+    const double *xc = hdg::p1_cycle(lev, dense, l - 1, nb, nu, w, s, rb);
     for (int k = 0; k < nu; ++k) {
         hdg::launch_p1_sweep(L.n, L.w, nb, L.col, L.val, L.diag, L.dinv, w, L.b, x, k == 0 ? xc : nullptr, L.parents,
-                             y, s);
+                             y, s, false, rb);
         std::swap(x, y);
     }
     return x;
 }
 
-hdg::DenseMap hdg::make_dense(hdg_ctx *c, int n, const double *src) {
-    hdg::DenseMap d;
-    const size_t nB = hdg::dense_doubles(n);
-    d.n = n;
-    d.B = dev_alloc<double>(c, nB);
-    HDG_HIP_CHECK(hipMemset(d.B, 0, nB * sizeof(double)));
-    if (src) hdg::launch_dense_cols(n, 0, n, src, d.B, nullptr);
+// n x n dense map at B from a row-major device matrix (src null: zeros), on the null stream
+static hdg::DenseMap fill_dense(int n, const double *src, double *B) {
+    HDG_HIP_CHECK(hipMemset(B, 0, hdg::dense_doubles(n) * sizeof(double)));
+    if (src) hdg::launch_dense_cols(n, 0, n, src, B, nullptr);
     check_launch();
+    hdg::DenseMap d;
+    d.n = n;
+    d.B = B;
+    return d;
+}
+
+hdg::DenseMap hdg::make_dense(hdg_ctx *c, int n, const double *src) {
+    const hdg::DenseMap d = fill_dense(n, src, dev_alloc<double>(c, hdg::dense_doubles(n)));
     HDG_HIP_CHECK(hipDeviceSynchronize());
     return d;
 }
 
+hdg::DenseMap hdg::make_dense(hdg_ctx *c, int n, const std::vector<double> &src) {
+    const size_t ld = hdg::dense_ld(n);
+    std::vector<double> B(hdg::dense_doubles(n), 0.0);
+    for (int i = 0; i < n; ++i) std::copy_n(&src[(size_t)i * n], n, &B[i * ld]);
+    hdg::DenseMap d;
+    d.n = n;
+    d.B = dev_upload(c, B);
+    return d;
+}
+
+// One level after the other, each from the map of the level below, so that a pass over
+// unit vectors is nine launches whatever the depth, and as many unit vectors to a pass as keep a
+// work vector within 8 MB.  Work vectors and lower maps lie in the Krylov basis, idle here: their
+// own allocations and releases took longer than the passes.  Whole setup of the level-5 sphere (p = 1,
+// 6 right-hand sides, 2562 vertices collapsed) 9.3-10.2 ms, 14.2-15.0 with every level by its own
+// kernels and 64 unit vectors a pass (865 launches), 8.3 without a collapsed level; 64x64 torus
+// (p = 2, 4; 1024 vertices) 5.2, 6.4 and 4.4.
 hdg::P1Dense hdg::collapse_p1(hdg_ctx *c, const std::vector<hdg::P1LevelDev> &lev, const double *inv, int max_n, int nu,
                               double w) {
-    hdg::P1Dense d;
-    d.map = hdg::make_dense(c, lev[0].n, inv);
     int top = 0;
     while (top + 1 < (int)lev.size() && lev[top + 1].n <= max_n) ++top;
-    if (top == 0) return d;
-    // the V-cycle applied to unit vectors, NCOL at a time, in work vectors of its own
-    constexpr int NCOL = COLLAPSE_COLS;
-    std::vector<hdg::P1LevelDev> t(lev.begin(), lev.begin() + top + 1);
-    for (auto &L : t) {
-        L.b = dev_alloc<double>(c, (size_t)3 * L.n * NCOL);
-        L.x = L.b + (size_t)L.n * NCOL;
-        L.y = L.x + (size_t)L.n * NCOL;
+    hdg::P1Dense d;
+    if (top == 0) {
+        d.map = hdg::make_dense(c, lev[0].n, inv);
+        return d;
     }
-    const int n = t[top].n;
-    hdg::P1Dense r;
-    r.top = top;
-    r.map = hdg::make_dense(c, n, nullptr);
-    for (int j = 0; j < n; j += NCOL) {
-        const int nc = std::min(NCOL, n - j);
-        hdg::launch_unit_cols(n, j, nc, t[top].b, nullptr);
-        const double *x = hdg::p1_cycle(t, d, top, nc, nu, w, nullptr);
-        hdg::launch_dense_cols(n, j, nc, x, r.map.B, nullptr);
+    std::vector<int> sizes;
+    for (int l = 0; l <= top; ++l) sizes.push_back(lev[l].n);
+    const hdg::CollapsePlan plan = hdg::plan_collapse(sizes, c->kV_len);
+    const bool own = plan.total > c->kV_len;
+    double *const scratch = own ? dev_alloc<double>(c, plan.total) : c->kV;
+    d.map = fill_dense(lev[0].n, inv, scratch + plan.map[0]);
+    for (int l = 1; l <= top; ++l) {
+        const int n = lev[l].n, nc = plan.cols[l];
+        std::vector<hdg::P1LevelDev> t{lev[l - 1], lev[l]};
+        double *p = scratch + plan.work;
+        for (auto &L : t) {
+            const size_t len = (size_t)L.n * nc;
+            L.b = p;
+            L.x = p + len;
+            L.y = p + 2 * len;
+            p += 3 * len;
+        }
+        const hdg::P1Dense coarse{d.map, 0};
+        d.map = fill_dense(n, nullptr, l < top ? scratch + plan.map[l] : dev_alloc<double>(c, hdg::dense_doubles(n)));
+        d.top = l;
+        for (int j = 0; j < n; j += nc) {
+            const int k = std::min(nc, n - j);
+            hdg::launch_unit_cols(n, j, k, t[1].b, nullptr);
+            hdg::launch_dense_cols(n, j, k, hdg::p1_cycle(t, coarse, 1, k, nu, w, nullptr, 4), d.map.B, nullptr);
+        }
+        check_launch();
     }
-    check_launch();
     HDG_HIP_CHECK(hipDeviceSynchronize());
-    for (auto &L : t) dev_release(c, L.b, sizeof(double) * 3 * (size_t)L.n * NCOL);
-    dev_release(c, d.map.B, sizeof(double) * hdg::dense_doubles(lev[0].n));
-    return r;
+    if (own) dev_release(c, scratch, sizeof(double) * plan.total);
+    return d;
 }
 
 void *hdg::ctx_alloc(hdg_ctx *c, size_t bytes) { return dev_alloc<char>(c, bytes); }

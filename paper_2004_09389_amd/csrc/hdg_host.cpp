@@ -501,6 +501,30 @@ struct P1Cycle {
 };
 }  // namespace
 
+int hdg::dense_ld(int n) { return (n + 1) / 2 * 2; }
+size_t hdg::dense_doubles(int n) { return (size_t)((n + 47) / 48 * 48) * hdg::dense_ld(n); }   // whole blocks of 4, 8, 12 or 16 rows
+
+hdg::CollapsePlan hdg::plan_collapse(const std::vector<int> &n, size_t have) {
+    constexpr int MIN_COLS = 64, VALUES = 1 << 20;   // a work vector of at most 8 MB
+    const int top = (int)n.size() - 1;
+    hdg::CollapsePlan P;
+    P.map.resize(n.size());
+    P.cols.resize(n.size());
+    for (int l = 0; l < top; ++l) {
+        P.map[l] = P.work;
+        P.work += hdg::dense_doubles(n[l]);
+    }
+    auto column = [&](int l) { return (size_t)3 * (n[l] + n[l - 1]); };
+    size_t need = P.work;
+    for (int l = 1; l <= top; ++l) need = std::max(need, P.work + std::min(n[l], MIN_COLS) * column(l));
+    P.total = std::max(have, need);
+    for (int l = 1; l <= top; ++l) {
+        const int fit = (int)std::min<size_t>((P.total - P.work) / column(l), VALUES / n[l]) / MIN_COLS * MIN_COLS;
+        P.cols[l] = std::min(n[l], std::max(MIN_COLS, fit));
+    }
+    return P;
+}
+
 std::vector<double> hdg::p1_vcycle_matrix(const std::vector<hdg::P1Host> &ops, const int32_t *const *parents, int nu,
                                           double omega) {
     const int n0 = ops[0].n;

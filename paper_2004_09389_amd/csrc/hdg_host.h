@@ -75,6 +75,18 @@ P1Host galerkin_coarsen(const P1Host &fine, const int32_t *parents, int nc);
 // transfers: the linear map the V-cycle applies to the finest level's right-hand side
 std::vector<double> p1_vcycle_matrix(const std::vector<P1Host> &ops, const int32_t *const *parents, int nu,
                                      double omega);
+// dense level maps (hdg_kernels.hip): row stride, and entries with padding
+int dense_ld(int n);
+size_t dense_doubles(int n);
+// Scratch of collapse_p1 for levels 0..top of n[l] vertices, in doubles: the maps of levels below
+// top at map[l], then, at work, three vectors on level l and on level l - 1 for cols[l] unit
+// vectors at a time.  have: doubles at hand; total exceeds it only where that is too few.
+struct CollapsePlan {
+    size_t total = 0, work = 0;
+    std::vector<size_t> map;
+    std::vector<int> cols;
+};
+CollapsePlan plan_collapse(const std::vector<int> &n, size_t have);
 // in-place inverse of a dense SPD matrix [n][n]; returns false when not positive definite
 bool spd_inverse(std::vector<double> &a, int n);
 // in-place inverse of a dense matrix [n][n] (Gauss-Jordan, partial pivoting); false when singular

@@ -114,13 +114,16 @@ void check_abi(int rc);
 // upload P1 operators (coarse to fine) with transfers and the coarsest dense inverse (hdg_api.hip)
 void build_p1_levels(hdg_ctx *c, const hdg_mesh *levels, const int32_t *const *parents,
                      const std::vector<P1Host> &ops, std::vector<P1LevelDev> &lev, double **coarse_inv);
-// one V-cycle on level l (input lev[l].b, FP64); returns the buffer holding the result
-double *p1_cycle(std::vector<P1LevelDev> &lev, const P1Dense &dense, int l, int nb, int nu, double w, hipStream_t s);
+// one V-cycle on level l (input lev[l].b, FP64; rb as for the P1 launchers); returns the buffer
+// holding the result
+double *p1_cycle(std::vector<P1LevelDev> &lev, const P1Dense &dense, int l, int nb, int nu, double w, hipStream_t s,
+                 int rb = 1);
 // The largest level of at most max_n vertices as a dense map: the V-cycle with nu sweeps of
 // damping w applied to unit vectors.  inv: the coarsest inverse, row-major (device); synchronous.
 P1Dense collapse_p1(hdg_ctx *c, const std::vector<P1LevelDev> &lev, const double *inv, int max_n, int nu, double w);
-// an n x n dense map of the context from a row-major device matrix (src null: zeros); synchronous
+// an n x n dense map of the context from a row-major device matrix or a host one; synchronous
 DenseMap make_dense(hdg_ctx *c, int n, const double *src);
+DenseMap make_dense(hdg_ctx *c, int n, const std::vector<double> &src);
 // device allocation owned by the context (freed by hdg_destroy)
 void *ctx_alloc(hdg_ctx *c, size_t bytes);
 // free one device allocation of the context
@@ -212,6 +215,7 @@ struct hdg_ctx {
     // Krylov work
     double *kr = nullptr, *kz = nullptr, *kp = nullptr, *kw = nullptr, *klam = nullptr;
     double *kV = nullptr, *kZ = nullptr;      // FGMRES bases [(restart+1)][vec], [restart][vec]
+    size_t kV_len = 0;                        // doubles of kV
     double *red = nullptr;                    // reduction partials of the dot products
     double *red2 = nullptr;                   // ... of the norms taken by the update kernels
     double *scal = nullptr;                   // device scalars [slot][max_rhs]

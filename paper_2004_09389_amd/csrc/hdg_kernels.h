@@ -205,10 +205,8 @@ void launch_p1_restrict(int nc, int nb, const int *crow, const int *ccol, const 
 void launch_p1_resid_restrict(int n, int W, const int *col, const double *val, const double *diag, const double *b,
                               const double *x, int nc, const int *crow, const int *ccol, const double *cw, double *bc,
                               hipStream_t s, bool f32 = false);
-// x = B b for a dense map; nb <= 64
+// x = B b for a dense map; any nb
 void launch_dense(const DenseMap &D, int nb, const double *b, double *x, hipStream_t s, bool f32 = false);
-int dense_ld(int n);                            // row stride of B
-size_t dense_doubles(int n);                    // entries of B, padding included
 void launch_dense_cols(int n, int col0, int ncol, const double *src, double *B, hipStream_t s);
 void launch_unit_cols(int n, int col0, int ncol, double *b, hipStream_t s);
 

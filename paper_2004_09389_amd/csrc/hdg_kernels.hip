@@ -2094,6 +2094,7 @@ __global__ __launch_bounds__(64 * DENSE_WAVES) void k_dense(int n, int ld, int n
     __shared__ double part[W][R * T * 64];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, i = lane & 3, kl = lane >> 2;
     const int row0 = blockIdx.x * 4 * R, nch = (ld + 31) / 32;
+    const int r0 = blockIdx.y * 16 * T;   // first right-hand side
     const bool quad = nb % 4 == 0;   // aligned groups of four right-hand sides
     double acc[R][T][4];
 #pragma unroll
@@ -2117,7 +2118,7 @@ __global__ __launch_bounds__(64 * DENSE_WAVES) void k_dense(int n, int ld, int n
                 const VT *bk = b + (size_t)min(k0 + h, n - 1) * nb;   // columns past n meet zeros of B
 #pragma unroll
                 for (int t = 0; t < T; ++t) {
-                    const int r = 16 * t + 4 * i;
+                    const int r = r0 + 16 * t + 4 * i;
                     if (quad && r < nb) {
                         load_raw<4>(bk + r, bv[u][h][t]);
                     } else {
@@ -2154,7 +2155,7 @@ __global__ __launch_bounds__(64 * DENSE_WAVES) void k_dense(int n, int ld, int n
             }
     __syncthreads();
     for (int o = tid; o < R * T * 64; o += 64 * W) {
-        const int r = o % (16 * T), row = row0 + o / (16 * T);
+        const int r = r0 + o % (16 * T), row = row0 + o / (16 * T);
         double s = 0.0;
 #pragma unroll
         for (int w = 0; w < W; ++w) s += part[w][o];
@@ -2707,16 +2708,14 @@ void launch_p1_resid_restrict(int n, int W, const int *col, const double *val, c
 #undef RR
 }
 #undef P1_GRID
-int dense_ld(int n) { return (n + 1) / 2 * 2; }
-size_t dense_doubles(int n) { return (size_t)((n + 47) / 48 * 48) * dense_ld(n); }   // whole blocks of 4, 8, 12 or 16 rows
 void launch_dense(const DenseMap &D, int nb, const double *b, double *x, hipStream_t s, bool f32) {
     const int n = D.n, ld = dense_ld(n);
     // Rows per block: as many blocks as CUs, and no more rows than that takes (1100 rows
     // belong to the first line: 1024 rows, 16 right-hand sides: four 4.0 us, eight 5.3 us).
     // V-cycle with 4 R rows for R = 2 / 3 / 4: 1600 rows, 6 right-hand sides 49.2 / - / 53.6 us,
     // 1936 rows, 4: 49.8 / - / 53.5; 2562 rows, 6: 65.3 / 61.0 / 63.4, 2: 53.6 / 50.9 / 52.9.
-#define DN(R, T) hipLaunchKernelGGL((k_dense<R, T, VT>), dim3((n + 4 * R - 1) / (4 * R)), dim3(64 * DENSE_WAVES), 0, s, n, \
-                                    ld, nb, D.B, pv<VT>(b), pv<VT>(x))
+#define DN(R, T) hipLaunchKernelGGL((k_dense<R, T, VT>), dim3((n + 4 * R - 1) / (4 * R), (nb + 16 * T - 1) / (16 * T)), \
+                                    dim3(64 * DENSE_WAVES), 0, s, n, ld, nb, D.B, pv<VT>(b), pv<VT>(x))
 #define DNT(R) if (nb <= 16) DN(R, 1); else if (nb <= 32) DN(R, 2); else DN(R, 4)
     P1_TYPED(if (nb == 1) hipLaunchKernelGGL(k_dense_row<VT>, dim3(n), dim3(256), 0, s, n, ld, D.B, pv<VT>(b), pv<VT>(x));
              else if (n <= 1100) { DNT(1); }
