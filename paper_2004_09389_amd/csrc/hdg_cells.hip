@@ -20,7 +20,7 @@
 // Measured (dense maps before): 256x256 torus, p = 3, one right-hand side: recovery 217 -> 42 us
 // (168 MB of cell data and vectors, 4.0 TB/s), condensation with its gather 83 -> 35 us; 16:
 // 721 -> 300 and 341 -> 267 us.  Level-6 sphere, p = 3: recovery at 1 / 3 / 8 / 16 / 32
-// right-hand sides 147 / 1244 / 601 / 470 / 645 -> 82 / 108 / 205 / 348 / 651 us.
+// right-hand sides 147 / 1244 / 601 / 470 / 645 -> 82 / 108 / 205 / 348 / 440 us.
 // One thread per (cell, right-hand side), right-hand side fastest; the tables are
 // wave-uniform (scalar loads), the cell factors are 16-byte loads, consecutive
 // cells in consecutive lanes.  All products are written as fma in one order, so
@@ -60,16 +60,29 @@ __device__ __forceinline__ void tie(ctab &tab, double &v) {
     if constexpr (ON) asm volatile("" : "+s"(tab), "+v"(v));
 }
 
+// A cell's factors, 16-byte pairs a fixed stride apart: in memory, or the block's copy in LDS
+typedef __attribute__((address_space(3))) const dbl2_t lds_pair;
+struct FromMem {
+    const dbl2_t *p;
+    size_t stride;
+    __device__ __forceinline__ dbl2_t operator[](int q) const { return p[q * stride]; }
+};
+struct FromLds {
+    lds_pair *p;
+    int stride;
+    __device__ __forceinline__ dbl2_t operator[](int q) const { return p[q * stride]; }
+};
+
 struct Geo {
     double j00, j01, j10, j11;   // k d(xi_r)/d(x_d)
     double ax[3], ay[3], b[3];   // k L n_x / |J|, k L n_y / |J|, k t L / |J| per facet
     double g;                    // |J| / k
 };
-__device__ __forceinline__ Geo load_geo(const double *geo, size_t NK, int K) {
-    const dbl2_t *p = reinterpret_cast<const dbl2_t *>(geo) + K;
+template <typename F>
+__device__ __forceinline__ Geo load_geo(const F &geo) {
     dbl2_t v[7];
 #pragma unroll
-    for (int q = 0; q < 7; ++q) v[q] = p[q * NK];
+    for (int q = 0; q < 7; ++q) v[q] = geo[q];
     return Geo{v[0].x, v[0].y, v[1].x, v[1].y, {v[2].x, v[3].x, v[4].x}, {v[2].y, v[3].y, v[4].y},
                {v[5].x, v[5].y, v[6].x}, v[6].y};
 }
@@ -128,12 +141,11 @@ __device__ __forceinline__ void sub_div(ctab tab, const Geo &g,
 
 // f uniform.  On entry w, y1, y2: the cell's right-hand side (hs r_h, r_u) less the trace
 // terms; on exit phi in w and u in y1, y2: v = Z y, w -= k D.v, phi = (Sigma^-1 M) w, u = v + Z t
-template <int P, bool TIE>
-__device__ __forceinline__ void cell_inverse(const CellFactors &c, ctab tab, const Geo &g,
-                                             size_t NK, int K, double (&w)[CellTab<P>::n],
-                                             double (&y1)[CellTab<P>::n], double (&y2)[CellTab<P>::n]) {
+template <int P, bool TIE, typename F>
+__device__ __forceinline__ void cell_inverse(const CellFactors &c, ctab tab, const Geo &g, const F &fs,
+                                             double (&w)[CellTab<P>::n], double (&y1)[CellTab<P>::n],
+                                             double (&y2)[CellTab<P>::n]) {
     constexpr int n = CellTab<P>::n;
-    const dbl2_t *fs = reinterpret_cast<const dbl2_t *>(c.fs) + K;
     double phi[n], t1[n], t2[n];
 #pragma unroll
     for (int i = 0; i < n; ++i) {
@@ -145,7 +157,7 @@ __device__ __forceinline__ void cell_inverse(const CellFactors &c, ctab tab, con
     sub_div<P, TIE>(tab, g, y1, y2, w);
 #pragma unroll
     for (int q = 0; q < (n * n + 1) / 2; ++q) {
-        const dbl2_t a = fs[q * NK];
+        const dbl2_t a = fs[q];
         phi[(2 * q) / n] = fm(a.x, w[(2 * q) % n], phi[(2 * q) / n]);
         if (2 * q + 1 < n * n) phi[(2 * q + 1) / n] = fm(a.y, w[(2 * q + 1) % n], phi[(2 * q + 1) / n]);
     }
@@ -162,22 +174,20 @@ __device__ __forceinline__ void cell_inverse(const CellFactors &c, ctab tab, con
 // (w, y), t += K phi_i; then u_i = Z_i (y + t).  The next row's loads are in flight while a
 // row is used; the row loops are not unrolled beyond that pair, or all their loads
 // would be hoisted to the front (500 registers).
-template <int P>
-__device__ __forceinline__ void cell_inverse_vf(const CellFactors &c, ctab tab, const Geo &g,
-                                                size_t NK, int K, const double (&w)[CellTab<P>::n],
-                                                double (&y1)[CellTab<P>::n], double (&y2)[CellTab<P>::n], int nb,
-                                                double *dst) {
+template <int P, typename F>
+__device__ __forceinline__ void cell_inverse_vf(const CellFactors &c, ctab tab, const Geo &g, const F &fs, const F &z,
+                                                const double (&w)[CellTab<P>::n], double (&y1)[CellTab<P>::n],
+                                                double (&y2)[CellTab<P>::n], int nb, double *dst) {
     constexpr int n = CellTab<P>::n, RW = (3 * n + 1) / 2;   // rows of 3 n padded to pairs
-    const dbl2_t *fs = reinterpret_cast<const dbl2_t *>(c.fs) + K, *z = reinterpret_cast<const dbl2_t *>(c.zt) + K;
     const double ih = 1.0 / c.hs;
     double t1[n], t2[n];
 #pragma unroll
     for (int i = 0; i < n; ++i) t1[i] = t2[i] = 0.0;
     auto in = [&](int j) { return j < n ? w[j] : (j < 2 * n ? y1[j - n] : y2[j - 2 * n]); };
     auto row = [&](int i, dbl2_t (&a)[RW]) {
-        const dbl2_t *p = fs + (size_t)(min(i, n - 1) * RW) * NK;
+        const int q0 = min(i, n - 1) * RW;
 #pragma unroll
-        for (int q = 0; q < RW; ++q) a[q] = p[q * NK];
+        for (int q = 0; q < RW; ++q) a[q] = fs[q0 + q];
     };
     auto use = [&](int i, const dbl2_t (&a)[RW]) {
         double p = 0.0;
@@ -207,9 +217,9 @@ __device__ __forceinline__ void cell_inverse_vf(const CellFactors &c, ctab tab, 
         y2[i] += t2[i];
     }
     auto zrow = [&](int i, dbl2_t (&a)[n]) {
-        const dbl2_t *p = z + (size_t)(min(i, n - 1) * n) * NK;
+        const int q0 = min(i, n - 1) * n;
 #pragma unroll
-        for (int j = 0; j < n; ++j) a[j] = p[j * NK];
+        for (int j = 0; j < n; ++j) a[j] = z[q0 + j];
     };
     auto zuse = [&](int i, const dbl2_t (&a)[n]) {
         double a1 = 0.0, a2 = 0.0;
@@ -233,10 +243,21 @@ __device__ __forceinline__ void cell_inverse_vf(const CellFactors &c, ctab tab, 
 }
 
 constexpr int CELL_THREADS = 256;
-// ST: cell vectors staged through LDS (few right-hand sides: a thread's values lie nc nb
-// doubles from its neighbour cell's); else read and written in place, whole
-// segments of right-hand sides at a time.  REC: recovery, else condensation.
-template <int P, bool VF, bool ST, bool REC>
+template <int P, bool VF>
+constexpr int FACTOR_PAIRS = 7 + (VF ? CellTab<P>::n * ((3 * CellTab<P>::n + 1) / 2) + CellTab<P>::n * CellTab<P>::n
+                                     : (CellTab<P>::n * CellTab<P>::n + 1) / 2);
+// What a block passes through LDS:
+//   CP_VECTORS  the cells' vectors: the inputs up to CELL_SMALL_RHS right-hand sides (a thread's
+//               values lie nc nb doubles from its neighbour cell's), the results always;
+//   CP_DIRECT   nothing: vectors are read and written in place, whole segments of right-hand
+//               sides at a time;
+//   CP_FACTORS  the cells' factors, vectors in place.  With many right-hand sides a wavefront's lanes
+//               read one or two cells' factors, and a 16-byte load returns 1 KB to them through L1 for
+//               the 16 or 32 it needs (f varying, p = 3: 257 loads, as long as the whole pass); from
+//               LDS half of that, and each factor comes from memory once per block.
+// REC: recovery, else condensation.
+constexpr int CP_VECTORS = 0, CP_DIRECT = 1, CP_FACTORS = 2;
+template <int P, bool VF, int MODE, bool REC>
 __global__ __launch_bounds__(CELL_THREADS) void k_cell_pass(int nk, int nb, CellFactors c,
                                                             const int *__restrict__ cell_facet,
                                                             const int8_t *__restrict__ cell_rev,
@@ -244,22 +265,34 @@ __global__ __launch_bounds__(CELL_THREADS) void k_cell_pass(int nk, int nb, Cell
                                                             const double *__restrict__ lam, double *__restrict__ out) {
     using T = CellTab<P>;
     constexpr int n = T::n, m = T::m, nc = 3 * n;
+    constexpr bool ST = MODE == CP_VECTORS, FL = MODE == CP_FACTORS;
+    constexpr int NF = (FACTOR_PAIRS<P, VF>) - 7 - (VF ? n * n : 0);   // pairs of fs
     extern __shared__ double sm[];
     const size_t NK = (size_t)nk;
     ctab tab = as_tab(c.tab);
-    const int cpb = ST ? CELL_THREADS / nb : 0, per = nc * nb;
+    const int cpb = MODE != CP_DIRECT ? CELL_THREADS / nb : 0, per = nc * nb;
     const int64_t t = (int64_t)xcd_block() * CELL_THREADS + threadIdx.x;
-    const int K0 = xcd_block() * cpb, cnt = ST ? min(cpb, nk - K0) : 0;
+    const int K0 = xcd_block() * cpb, cnt = MODE != CP_DIRECT ? min(cpb, nk - K0) : 0;
     int cl, r, K;
     bool live;
-    if constexpr (ST) {
+    if constexpr (MODE != CP_DIRECT) {
         if (cnt <= 0) return;   // the whole block
         cl = threadIdx.x / nb;
         r = threadIdx.x - cl * nb;
         K = K0 + cl;
         live = cl < cnt;
-        if (nb <= CELL_SMALL_RHS) {
+        if (ST && nb <= CELL_SMALL_RHS) {
             stage_cells(rc + (size_t)K0 * per, sm, cnt * per);
+            __syncthreads();
+        }
+        if constexpr (FL) {
+            dbl2_t *dst = reinterpret_cast<dbl2_t *>(sm);
+            for (int i = threadIdx.x; i < (FACTOR_PAIRS<P, VF>) * cpb; i += CELL_THREADS) {
+                const int q = i / cpb, k = min(K0 + i - q * cpb, nk - 1);
+                const double *src = q < 7 ? c.geo : (q < 7 + NF ? c.fs : c.zt);
+                const int o = q < 7 ? q : (q < 7 + NF ? q - 7 : q - 7 - NF);
+                dst[i] = reinterpret_cast<const dbl2_t *>(src)[o * NK + k];
+            }
             __syncthreads();
         }
     } else {
@@ -270,7 +303,11 @@ __global__ __launch_bounds__(CELL_THREADS) void k_cell_pass(int nk, int nb, Cell
         if (!live) return;
     }
     if (live) {
-        const Geo g = load_geo(c.geo, NK, K);
+        auto factor = [&](const double *src, int q) {
+            if constexpr (FL) return FromLds{(lds_pair *)sm + q * cpb + cl, cpb};
+            else return FromMem{reinterpret_cast<const dbl2_t *>(src) + K, NK};
+        };
+        const Geo g = load_geo(factor(c.geo, 0));
         double w[n], y1[n], y2[n];
         const double *src = ST && nb <= CELL_SMALL_RHS ? sm + cl * per + r : rc + (size_t)K * per + r;
 #pragma unroll
@@ -301,8 +338,8 @@ __global__ __launch_bounds__(CELL_THREADS) void k_cell_pass(int nk, int nb, Cell
             }
         }
         double *dst = ST ? sm + cl * per + r : out + (size_t)K * per + r;
-        if constexpr (VF) cell_inverse_vf<P>(c, tab, g, NK, K, w, y1, y2, nb, dst);
-        else cell_inverse<P, REC>(c, tab, g, NK, K, w, y1, y2);
+        if constexpr (VF) cell_inverse_vf<P>(c, tab, g, factor(c.fs, 7), factor(c.zt, 7 + NF), w, y1, y2, nb, dst);
+        else cell_inverse<P, REC>(c, tab, g, factor(c.fs, 7), w, y1, y2);
         if constexpr (VF) {
         } else if constexpr (REC) {
             const double ih = 1.0 / c.hs;
@@ -358,7 +395,7 @@ __global__ __launch_bounds__(CELL_THREADS) void k_cell_tendency(int nk, int nb, 
     if (K >= nk) return;
     const size_t NK = (size_t)nk;
     ctab tab = as_tab(c.tab);
-    const Geo g = load_geo(c.geo, NK, K);
+    const Geo g = load_geo(FromMem{reinterpret_cast<const dbl2_t *>(c.geo) + K, NK});
     double phi[n], u1[n], u2[n], d0[n], d1[n], d2[n];   // d = r - q
     const double *src = q + (size_t)K * nc * nb + r;
 #pragma unroll
@@ -527,17 +564,38 @@ void launch_pass(int nk, int nb, const CellFactors &c, const int *cell_facet, co
                  const double *lam, double *out, hipStream_t s) {
     constexpr int nc = 3 * CellTab<P>::n;
     auto grid8 = [](int64_t blocks) { return dim3((unsigned)((blocks + N_XCD - 1) / N_XCD * N_XCD)); };
-    // f varying: always through LDS, as the row loops write their outputs one by one (a store to
-    // memory there holds up the next row's loads, which the same counter waits for)
-    if (VF || nb <= CELL_SMALL_RHS) {
-        const int cpb = CELL_THREADS / nb;
-        hipLaunchKernelGGL((k_cell_pass<P, VF, true, REC>), grid8((nk + cpb - 1) / cpb), dim3(CELL_THREADS),
-                           sizeof(double) * cpb * nc * nb, s, nk, nb, c, cell_facet, cell_rev, rc, lam, out);
-    } else if constexpr (!VF) {
-        hipLaunchKernelGGL((k_cell_pass<P, VF, false, REC>),
-                           grid8(((int64_t)nk * nb + CELL_THREADS - 1) / CELL_THREADS), dim3(CELL_THREADS), 0, s, nk, nb,
-                           c, cell_facet, cell_rev, rc, lam, out);
+    const int cpb = CELL_THREADS / nb;
+    const size_t vectors = sizeof(double) * cpb * nc * nb, factors = (size_t)16 * (FACTOR_PAIRS<P, VF>) * cpb;
+#define GO(MODE, BYTES)                                                                                            \
+    hipLaunchKernelGGL((k_cell_pass<P, VF, MODE, REC>),                                                            \
+                       grid8(MODE == CP_DIRECT ? ((int64_t)nk * nb + CELL_THREADS - 1) / CELL_THREADS              \
+                                               : (nk + cpb - 1) / cpb),                                            \
+                       dim3(CELL_THREADS), BYTES, s, nk, nb, c, cell_facet, cell_rev, rc, lam, out)
+    if constexpr (VF) {
+        // Factors through LDS as soon as they fit (p = 3: from 17 right-hand sides on); else results
+        // through LDS, as the row loops write them one by one (a store to memory there holds up the next
+        // row's loads, which the same counter waits for).  Recovery on the level-6 sphere, results / factors
+        // (dense maps): p = 1 at 16, 32, 64 right-hand sides 65 / 49 (56), 138 / 103 (108), 252 / 186 (192) us;
+        // p = 2 168 / 125 (195), 315 / 207 (298), 596 / 363 (461); p = 3 at 20, 32, 64
+        // 432 / 339 (555), 644 / 440 (619), 1225 / 718 (953).
+        if (nb > CELL_SMALL_RHS && factors <= 65536) GO(CP_FACTORS, factors);
+        else GO(CP_VECTORS, vectors);
+    } else if (nb <= CELL_SMALL_RHS) {
+        GO(CP_VECTORS, vectors);
+    } else {
+        // Condensation at p = 3, where a wavefront has at most two cells: 200x200 torus, direct / factors
+        // (dense map): 32 right-hand sides 301 / 273 (302), 64 553 / 499 (524) us; 96x96 61.5 / 63.1 (62), 48
+        // 106 / 96 (97), 64 140 / 129 (129); at 9 to 28 the direct form is up to 1.14 times faster there.
+        // The recovery has fewer wavefronts with it (200x200, 16: 184 / 205).
+        if constexpr (!REC && P == 3) {
+            if (nb > 32) {
+                GO(CP_FACTORS, factors);
+                return;
+            }
+        }
+        GO(CP_DIRECT, 0);
     }
+#undef GO
 }
 
 }  // namespace
