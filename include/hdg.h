@@ -262,7 +262,9 @@ int hdg_mg_vcycle(hdg_ctx *ctx, int32_t nrhs, int32_t precision, const double *r
 /* Step 2: solve S lam = rhat to ||rhat - S lam|| <= rtol ||rhat|| per RHS.
  * lam is the initial guess on entry (device, [n_facet][facet_dofs][nrhs]) and the
  * solution on exit.  info: (host) [nrhs], may be NULL.  Returns when lam and info
- * are complete (as hdg_stage_solve). */
+ * are complete (as hdg_stage_solve).  While it runs, the calling thread watches for the
+ * residual norms in host memory (a spin wait of up to 2 s each, then the stream), so it
+ * keeps one core busy; so do hdg_stage_solve and hdg_imex_run. */
 int hdg_solve(hdg_ctx *ctx, int32_t nrhs, const double *rhat, double *lam,
               hdg_solve_info *info, void *stream);
 

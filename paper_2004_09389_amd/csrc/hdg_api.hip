@@ -630,7 +630,10 @@ const double *wait_lag(hdg_ctx *c, int slot, int nb, hipStream_t s) {
     for (int r = 0; r < nb;) {
         if (h[r] != LAG_PENDING) {
             ++r;
-        } else if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(2)) {
+            continue;
+        }
+        __builtin_ia32_pause();   // leaves the core's resources to its other thread
+        if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(2)) {
             HDG_HIP_CHECK(hipStreamSynchronize(s));
             for (; r < nb; ++r)
                 if (h[r] == LAG_PENDING) throw Error{HDG_EHIP, "a reduction wrote no result"};
