@@ -185,10 +185,10 @@ typedef struct {
     double  lambda_max;         /* eigenvalue estimate of D^-1 S (Chebyshev smoother), else 0 */
     int32_t persistent;         /* 1 when the context qualifies for the single-launch solve: upwind
                                    flux, at most 8 P1 levels and the LDS footprint of one workgroup
-                                   (10 trace vectors, 3 vectors per P1 level and 12.6 KiB of Krylov
+                                   (12 trace vectors, 3 vectors per P1 level and 13.6 KiB of Krylov
                                    scalars) within the device's LDS per workgroup less 2 KiB
-                                   (160 KiB on gfx950): up to about 1800 trace unknowns, e.g. the
-                                   8x8 torus at p = 1..3 and the 16x16 torus at p = 1 */
+                                   (160 KiB on gfx950): up to about 1400 trace unknowns, e.g. the
+                                   8x8 torus at p = 1..3 and the 15x15 torus at p = 1 */
 } hdg_sizes;
 
 /* ------------------------------------------------------------------ entry points */

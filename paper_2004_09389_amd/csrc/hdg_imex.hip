@@ -100,26 +100,27 @@ __global__ __launch_bounds__(256) void k_dg_half(int nk, int nb, int geom, doubl
 
 // Local trace index of unknown a of local facet i for a cell running along
 // (rev = 0) or against (rev = 1) the facet's direction.
-template <int P, int NU>
+constexpr int TEND_NU = 2;   // trace components per node (Lax-Friedrichs; the upwind form is k_cell_tendency)
+template <int P>
 __device__ __forceinline__ int tend_loc(int i, int a, int rev) {
     constexpr int m = P + 1;
     const int k = a % m;
-    return i * NU * m + (a - k) + (rev ? P - k : k);
+    return i * TEND_NU * m + (a - k) + (rev ? P - k : k);
 }
 
 // out = scale (q - r) with r the right-hand side for which the recovery
 // q = Ar r - Wr lam returns q:  Ar r = q + Wr lam,  solved per cell by
 // Gauss-Jordan with partial pivoting in LDS (one wavefront per cell, all
 // right-hand sides as extra columns).
-template <int P, int NU>
+template <int P>
 __global__ __launch_bounds__(64) void k_dg_tendency(int nk, int nb, double scale, const double *__restrict__ Ar,
                                                     const double *__restrict__ Wr,
                                                     const int *__restrict__ cell_facet,
                                                     const int8_t *__restrict__ cell_rev,
                                                     const double *__restrict__ q, const double *__restrict__ half,
                                                     double *__restrict__ out, int *__restrict__ err) {
-    constexpr int n = (P + 1) * (P + 2) / 2, m = P + 1, nc = 3 * n, M = NU * m, nt = 3 * M;
-    // LDS sized for the call's nb (tend_lds_bytes): [nc][nc + nb] | [nt][nb] | [nc]
+    constexpr int n = (P + 1) * (P + 2) / 2, m = P + 1, nc = 3 * n, M = TEND_NU * m, nt = 3 * M;
+    // LDS sized for the call's nb: [nc][nc + nb] | [nt][nb] | [nc]
     extern __shared__ double tsm[];
     const int LD = nc + nb, W = nc + nb;
     double *aug = tsm, *lam = tsm + nc * LD, *fac = lam + nt * nb;
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(64) void k_dg_tendency(int nk, int nb, double scale
         const int g = idx / nb, r = idx - g * nb, i = g / M, a = g - i * M;
         const int e = cell_facet[i * NK + K], rev = cell_rev[i * NK + K];
         const double v = half[(((size_t)e * 2 + 0) * M + a) * nb + r] + half[(((size_t)e * 2 + 1) * M + a) * nb + r];
-        lam[tend_loc<P, NU>(i, a, rev) * nb + r] = v;
+        lam[tend_loc<P>(i, a, rev) * nb + r] = v;
     }
     for (int idx = lane; idx < nc * nc; idx += 64) aug[(idx / nc) * LD + idx % nc] = Ar[(size_t)idx * NK + K];
     __syncthreads();
@@ -285,7 +286,7 @@ void dg_tendency(hdg_ctx *c, int nb, double dt, const double *q, double *out, hi
     HDG_HIP_CHECK(hipMemsetAsync(err, 0, sizeof(int), s));
     const size_t lds = (size_t)(c->nc * (c->nc + nb) + c->nt * nb + c->nc) * sizeof(double);
 #define TEND(P)                                                                                                   \
-    hipLaunchKernelGGL((k_dg_tendency<P, 2>), dim3(c->n_cell), dim3(64), lds, s, c->n_cell, nb, scale, c->Ar, c->Wr, \
+    hipLaunchKernelGGL((k_dg_tendency<P>), dim3(c->n_cell), dim3(64), lds, s, c->n_cell, nb, scale, c->Ar, c->Wr, \
                        c->cell_facet, c->cell_rev, q, half, out, err)
     switch (c->p) {
         case 1: TEND(1); break;

@@ -48,13 +48,14 @@ constexpr int P1_TAIL_MAX = 4096;       // upper bound of the option p1_tail_max
 // The P1 levels of at most p1_collapse_max vertices, taken together, are one dense product
 // (k_dense) instead of 4-6 launches of 4-5 us for each of them.  The product reads 8 n^2 bytes,
 // so the line lies where that takes about as long as the launches it replaces, and that
-// depends on where the matrix is found.  In the Infinity Cache: V-cycle of the level-5 sphere
+// depends on where the matrix is found.  In the Infinity Cache, whole solves: level-5 sphere
 // (p = 1, FP64, 1 / 6 / 16 right-hand sides) with its 2562-vertex level collapsed
-// 48 / 62 / 76 us, its 642-vertex level 49 / 69 / 85 us, none 59 / 87 / 102 us; 56x56 torus
-// (p = 2, 1 / 4) with its 3136-vertex level 38.8 / 65 us, its 784-vertex level 37.0 / 61 us.
-// In HBM (level-6 sphere, p = 2, 16 right-hand sides, whose vectors fill that cache): a
-// solve with 2562 vertices collapsed 3868 us, 642 vertices 3763 us.  Hence what the operator
-// rows and about 24 vectors leave free of 192 MiB, between 1100 (10 MB) and 2600 vertices.
+// 724 / 946 / 1237 us, its 642-vertex level 742 / 978 / 1290 us, none 900 / 1223 / 1552 us; 56x56
+// torus (p = 2, 1 / 4) with its 3136-vertex level 670 / 888 us, its 784-vertex level
+// 624 / 863 us, none 764 / 1095 us.  In HBM (level-6 sphere, p = 2, 16 right-hand sides, mixed with
+// refinement, whose vectors fill that cache) 2562 vertices gain nothing for their 52 MB: 3045 us,
+// 642 vertices 3065 us.  Hence what the operator rows and about 24 vectors leave free of 192 MiB,
+// between 1100 (10 MB) and 2600 vertices.
 constexpr int P1_COLLAPSE_MIN = 1100, P1_COLLAPSE_MAX = 2600;
 int p1_collapse_max(const hdg_ctx *c);
 constexpr int SMALL_LEVELS = 8;         // P1 levels of the single-launch solve

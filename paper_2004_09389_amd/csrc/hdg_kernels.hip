@@ -1517,8 +1517,9 @@ __global__ void k_sqrt(int nb, const double *__restrict__ in, double *__restrict
 // sides of one facet.  Block = F facets x (nb / RB) threads.
 //
 // What bounds them is memory, through the latency of four neighbour fetches in
-// turn: few registers (eight waves per SIMD) hide it better than more values
-// per thread or all fetches at once.  A thread takes 16 bytes of each vector
+// turn: few registers hide it better than more values per thread or all fetches at
+// once (the operator runs at eight waves per SIMD, the FP32-vector and FP64 sweeps at
+// p = 3 at six).  A thread takes 16 bytes of each vector
 // (RB = 2 FP64 or 4 FP32 values) where the batch divides, so that neighbouring
 // lanes read neighbouring bytes.  FP64 operator, 491520 facets, p = 3, 32
 // right-hand sides: RB = 4 310 us (4.3 TB/s, every other 16 bytes of a line left
@@ -1526,7 +1527,8 @@ __global__ void k_sqrt(int nb, const double *__restrict__ in, double *__restrict
 // large copy); the FP32 sweep there: RB = 2 212 us, RB = 4 175 us (6 TB/s).
 // 122880 facets, p = 3, 4 right-hand sides: RB = 4 48, RB = 2 25, one thread per
 // (facet, rhs) 30 us.  All five facets' values in registers at once (101-128
-// registers): 1.3 times slower at 32 right-hand sides, p = 2.
+// registers) was 1.3 times slower at 32 right-hand sides, p = 2, the one point where
+// it was tried.
 template <typename MT>
 __device__ __forceinline__ float lds_entry_f(const MT *p) { return (float)*p; }
 template <>

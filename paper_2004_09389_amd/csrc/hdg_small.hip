@@ -855,7 +855,7 @@ __device__ void publish_image(const SmallArgs &A, Ops *ops, const char *c) {
 }
 
 // Whole facets from global memory: told that more than two wavefronts per SIMD are of no use,
-// the compiler keeps 233 registers and the loads in flight that they hold (163 without:
+// the compiler keeps 226 registers and the loads in flight that they hold (163 without:
 // stage on a one-level 12 x 12 torus, f = 1, 346 us against 329).
 template <int OL>
 constexpr int MAX_WAVES = OL == OPS_FACETS ? 2 : 8;
