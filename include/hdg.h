@@ -151,7 +151,7 @@ typedef struct {
                                    fixed linear map, formed at setup (default 4096, max 4096, 0 =
                                    never: every level by its own kernels; the library itself stops
                                    between 1100 and 2600 vertices, by the memory a solve streams).
-                                   Forming it adds up to about 1 ms to hdg_setup and holds 8 bytes
+                                   Forming it adds 1-2 ms to hdg_setup at most and holds 8 bytes
                                    times the square of the vertices */
     int32_t p1_galerkin;        /* (upwind flux only) 0: the rediscretised coarse form (1/kappa)(M_1 + kappa^2 K_1) on
                                    every P1 level (default); 1: the Galerkin form S_c = pi^T S pi on
