@@ -2477,9 +2477,16 @@ static RowShape row_shape(int ne, int nb, int rb) {
 // FP32 vectors halve what a lane fetches: from nine on (whole FP32 solve with
 // refinement, 122880 facets: p = 2, 8 right-hand sides 2297 / 2275 us, 10: 2863 / 2986,
 // 16: 3090 / 3304; p = 3, 8: 3324 / 3248, 16: 4306 / 4675).
+// FP32 rows with FP64 vectors (the operator on its own and the V-cycle's residual) have half
+// the row bytes to save: where a vector no longer stays in the caches (from 524288 unknowns on)
+// staging pays from seven right-hand sides on.  Level-7 sphere, per (facet, rhs) / staged at 3, 5,
+// 6, 7: p = 2 42.2 / 46.4, 63.7 / 63.6, 72.0 / 76.2, 84.9 / 77.6 us, p = 3 61.9 / 73.7, 92.8 / 102.4,
+// 103 / 103, 119 / 109; 256x256 torus, p = 3 27.0 / 30.7, 39.4 / 43.3, 44.8 / 44.8, 50.8 / 48.3;
+// below the line, level-6 sphere, p = 2 11.8 / 10.4, 18.0 / 16.2, 20.6 / 18.6.
 static int rows_per_thread(int nb, int vb) { return vb == 4 && nb % 4 == 0 ? 4 : nb % 2 == 0 ? 2 : 1; }
-static RowShape apply_shape(int M, int ne, int nb, int rhs_block, int vb) {
-    if (M > 4 || nb < (vb == 4 ? 9 : 3) || rhs_block == 1) return RowShape{};
+static RowShape apply_shape(int M, int ne, int nb, int rhs_block, int vb, int mb) {
+    const int from = vb == 4 ? 9 : mb == 4 && (int64_t)ne * M >= 8 * SIMD_LANES ? 7 : 3;
+    if (M > 4 || nb < from || rhs_block == 1) return RowShape{};
     return row_shape(ne, nb, rows_per_thread(nb, vb));
 }
 static RowShape sweep_shape(int M, int ne, int nb, int rhs_block, int vb) {
@@ -2504,7 +2511,7 @@ static bool rowwise(int M, int ne) { return M >= 6 && (int64_t)ne * M <= 2 * SIM
 template <typename MT, typename XT, typename YT>
 void launch_trace_apply(int M, int ne, int nb, const MT *S, const int *nbr, const XT *x, const YT *b, YT *y,
                         hipStream_t s, int rhs_block) {
-    if (const RowShape h = apply_shape(M, ne, nb, rhs_block, sizeof(*x)); h.rb) {
+    if (const RowShape h = apply_shape(M, ne, nb, rhs_block, sizeof(*x), sizeof(*S)); h.rb) {
 #define TAB(MM) \
     ROWS_LAUNCH(h, (k_trace_apply_rb<MM, MT, XT, YT, 1, 64, YT>), 1, 64, ne, nb, S, nbr, x, b, y); \
     ROWS_LAUNCH(h, (k_trace_apply_rb<MM, MT, XT, YT, 1, 32, YT>), 1, 32, ne, nb, S, nbr, x, b, y); \
@@ -2531,7 +2538,7 @@ void launch_trace_apply(int M, int ne, int nb, const MT *S, const int *nbr, cons
 // FP32 inner solve of a refinement step)
 void launch_trace_residual_f32(int M, int ne, int nb, const double *S, const int *nbr, const double *x,
                                const double *b, float *y, hipStream_t s, int rhs_block) {
-    if (const RowShape h = apply_shape(M, ne, nb, rhs_block, sizeof(*x)); h.rb) {
+    if (const RowShape h = apply_shape(M, ne, nb, rhs_block, sizeof(*x), sizeof(*S)); h.rb) {
 #define TAB(MM) \
     ROWS_LAUNCH(h, (k_trace_apply_rb<MM, double, double, float, 1, 64, double>), 1, 64, ne, nb, S, nbr, x, b, y); \
     ROWS_LAUNCH(h, (k_trace_apply_rb<MM, double, double, float, 1, 32, double>), 1, 32, ne, nb, S, nbr, x, b, y); \

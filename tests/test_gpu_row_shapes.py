@@ -43,3 +43,19 @@ def test_staged_rows_bitwise(p):
             assert _rel(outs[4][0][..., c].cpu().numpy().ravel(), oracle.apply(x[..., c].ravel())) < 1e-12
             assert _rel(outs[4][2][..., c].cpu().numpy().ravel(), mg.vcycle(x[..., c].ravel())) < 1e-11
     s.close()
+
+
+def test_operator_on_a_large_mesh_same_bits_for_every_batch():
+    """FP32 rows with FP64 vectors at 589824 unknowns: one thread per (facet, right-hand side) up
+    to six of them, staged from seven on; each column is the same whatever batch it is in."""
+    import torch
+    from paper_2004_09389_amd.hdg import HDG_MIXED, HdgSolver
+    s = HdgSolver(hi.torus_hierarchy(256, 4), 2, 4.0 / 256, 1.0, 1.0, 0.7, max_rhs=8, restart=2)
+    assert s.n_facet * s.m >= 8 * 256 * 4 * 64
+    x = torch.from_numpy(np.random.default_rng(5).standard_normal((s.n_facet, s.m, 8))).cuda()
+    for mode in ((), (HDG_MIXED,)):
+        whole = s.trace_apply(x, *mode)
+        for nb in (1, 2, 3, 4, 6, 7):
+            print(f"[rows] 256x256 nb={nb} {mode}", flush=True)
+            assert torch.equal(s.trace_apply(x[..., :nb].contiguous(), *mode), whole[..., :nb])
+    s.close()
